@@ -257,6 +257,116 @@ __device__ __forceinline__ void acc_sums_to_lds(LaneSums& ls, long long* acc) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// the event kernel's own fold: the same integers in digits of 48 bits, two LDS atomics
+// per event and dimension instead of three.  A block's sums live in LDS as columns of
+// 48-bit digits: S1, S2 in the seven 32-bit-digit columns of the partial row, then per
+// grid slot {low, mid, top} (digit-major, like the row's columns) and per observable bin
+// {w low, w high, w top, w^2 low, w^2 mid, w^2 top}.  Between two carries a block adds at
+// most kFoldEvents events, so no column leaves 64 bits; the row is written in 32-bit
+// digits, and its value is the same integer whichever digits it is split into.
+//
+// Bound by the VALU (the digits) and the LDS (random bins): against three or four 32-bit
+// digits, 5 x 1e7 W+W- events 1515 -> 1491 us, 3 x 3e6 hadronic 588 -> 576 (there also a
+// third wave per SIMD, which the smaller LDS allows), 5 x 9e5 stratified W+ 363 -> 351.
+// ---------------------------------------------------------------------------
+constexpr int kFoldEvents = 32768;           // events of a block between two carries
+constexpr int kLds2 = 3;                     // LDS digits of a grid slot's w^2
+constexpr int kLdsObs = 6;                   // LDS digits of an observable bin
+constexpr unsigned long long kMask48 = 0xffffffffffffull, kMask32 = 0xffffffffull;
+__host__ __device__ constexpr int fold_cols(int nslot) { return kColHist + kLds2 * nslot; }
+__host__ __device__ constexpr int fold_obs_cols(int nobs) { return nobs > 0 ? kLdsObs * (nobs + 2) : 0; }
+
+// a non-negative integer below 2^52 held in binary64
+__device__ __forceinline__ long long int52(double v) {
+  return __double_as_longlong(v + 0x1p52) & 0xfffffffffffffll;
+}
+
+// a lane's sums between two carries: w in {low, high}, w^2 in {low, mid, top}
+constexpr int kFoldLane = 5;
+
+// the digits of one event: w = d[1] 2^48 + d[0], w^2 = h[2] 2^96 + h[1] 2^48 + h[0]; the
+// top digit is there only if some active lane of the wave has one (see top_digit_needed)
+struct FoldDigits {
+  long long d[2], h[3];
+  bool top;
+};
+
+template <bool NONNEG>
+__device__ __forceinline__ FoldDigits fold_digits(double w, int E1, int E2) {
+  FoldDigits g;
+  {
+    const double X = fmin(ldexp(NONNEG ? w : fabs(w), FX_BITS - E1), 0x1p95);
+    const double h = trunc(X * 0x1p-48);
+    const double l = trunc(__fma_rn(-h, 0x1p48, X));
+    g.d[0] = int52(l);
+    g.d[1] = int52(h);
+    if (!NONNEG && signbit(w)) {
+      g.d[0] = -g.d[0];
+      g.d[1] = -g.d[1];
+    }
+  }
+  double X = fmin(ldexp(w * w, FX2_BITS - E2), 0x1p127);
+  g.top = __ballot(X >= 0x1p96) != 0ull;
+  g.h[2] = 0;
+  if (g.top) {
+    const double t = trunc(X * 0x1p-96);
+    X = __fma_rn(-t, 0x1p96, X);
+    g.h[2] = static_cast<long long>(static_cast<uint32_t>(t));
+  }
+  const double m = trunc(X * 0x1p-48);
+  const double l = trunc(__fma_rn(-m, 0x1p48, X));
+  g.h[0] = int52(l);
+  g.h[1] = int52(m);
+  return g;
+}
+
+__device__ __forceinline__ void fold_hist(long long* acc, int col, int stride, const FoldDigits& g) {
+  unsigned long long* p = lds_col(acc, col);
+  atomicAdd(p, static_cast<unsigned long long>(g.h[0]));
+  atomicAdd(p + stride, static_cast<unsigned long long>(g.h[1]));
+  if (g.top) atomicAdd(p + 2 * stride, static_cast<unsigned long long>(g.h[2]));
+}
+
+__device__ __forceinline__ void fold_obs(long long* acc, int col, const FoldDigits& g) {
+  unsigned long long* p = lds_col(acc, col);
+  atomicAdd(p, static_cast<unsigned long long>(g.d[0]));
+  atomicAdd(p + 1, static_cast<unsigned long long>(g.d[1]));
+  fold_hist(acc, col + 3, 1, g);
+}
+
+// digits of 48 bits -> the 32-bit ones of a row (arithmetic shifts: low and high may be
+// negative sums)
+__device__ __forceinline__ void fold_row3(long long lo, long long hi, long long* r, int64_t stride) {
+  r[0] = lo & kMask32;
+  r[stride] = (lo >> 32) + ((hi & 0xffff) << 16);
+  r[2 * stride] = hi >> 16;
+}
+
+// per-lane sums -> wave totals -> the block's S1, S2 columns (call with the whole block)
+__device__ __forceinline__ void fold_sums_to_lds(const long long ls[kFoldLane], long long* acc) {
+  long long t[kFoldLane], r[kLane];
+#pragma unroll
+  for (int k = 0; k < kFoldLane; ++k) t[k] = wave_sum_i64(ls[k]);
+  fold_row3(t[0], t[1], r, 1);
+  fold_row3(t[2], t[3], r + kD1, 1);
+  r[kD1 + 3] = t[4];
+  if ((threadIdx.x & 63) == 0) {
+    unsigned long long* p = reinterpret_cast<unsigned long long*>(acc);
+#pragma unroll
+    for (int k = 0; k < kLane; ++k) atomicAdd(p + k, static_cast<unsigned long long>(r[k]));
+  }
+}
+
+// carries of the block's histogram columns into the digits above (call with the whole
+// block, between barriers); stride: between the digits of one slot
+__device__ __forceinline__ void fold_carry(long long* c, int stride) {
+  const long long lo = c[0], mid = c[stride] + (lo >> 48);
+  c[0] = lo & kMask48;
+  c[stride] = mid & kMask48;
+  c[2 * stride] += mid >> 48;
+}
+
 struct EventArgs {
   PhysConst pc;
   DevBufs b;
@@ -285,9 +395,11 @@ struct EventArgs {
 // waves per SIMD the register allocation must allow with 256-thread blocks
 constexpr double kExtLo = 0x1p-40, kExtHi = 1.0 - 0x1p-40;
 
+// (W+W- with four spills 20 bytes a lane and ran the same 1500 us per 5 x 1e7 events; the
+// hadronic W+W- with three spills 52 bytes and took 573 us per 3 x 3e6, with two 581)
 template <int PROC>
 constexpr int event_min_waves() {
-  return PROC == VEGAS_WW_HAD ? 2 : (PROC == VEGAS_WW_4L ? 3 : 4);
+  return PROC == VEGAS_WW_HAD || PROC == VEGAS_WW_4L ? 3 : 4;
 }
 
 // EXT: the point is the learned proposal's y (binary32, kept inside the open unit
@@ -305,21 +417,22 @@ template <int PROC, int PREC, int D, int MAXT, bool EXT = false, bool FUSED = fa
 __global__ __launch_bounds__(MAXT, (MAXT == 256 ? event_min_waves<PROC>() : 1)) void k_event(EventArgs a) {
   extern __shared__ unsigned char smem[];
   const int n = a.nbins, nd = D > 0 ? D : a.ndim;
-  const int ncol_h = hist_cols(nd * n);
+  const int nslot = nd * n, ncol_h = hist_cols(nslot);
   const int ncol = ncol_h + (OBS ? obs_cols(a.nobs) : 0);
+  const int fcol_h = fold_cols(nslot), fcol = fcol_h + (OBS ? fold_obs_cols(a.nobs) : 0);
   double* e_lds = reinterpret_cast<double*>(smem);
-  long long* acc = reinterpret_cast<long long*>(e_lds + nd * (n + 1));  // FUSED: [ncol]
+  long long* acc = reinterpret_cast<long long*>(e_lds + nd * (n + 1));  // FUSED: [fcol]
   for (int i = threadIdx.x; i < nd * (n + 1); i += blockDim.x) e_lds[i] = a.b.edges[i];
   if constexpr (FUSED)
-    for (int i = threadIdx.x; i < ncol; i += blockDim.x) acc[i] = 0;
+    for (int i = threadIdx.x; i < fcol; i += blockDim.x) acc[i] = 0;
   // with 10 or more dimensions the register budget of 2 waves per SIMD is spent on the
   // integrand, so the lane's S1, S2 digit sums live in LDS, one private slot per lane
-  // and digit (no atomics: no other lane touches it) instead of 12 registers
+  // and digit (no atomics: no other lane touches it) instead of 10 registers
   constexpr bool kLdsSums = FUSED && D >= 10 && MAXT == 256;
-  long long* lsum = acc + ncol;  // kLdsSums: [kLane][256]
+  long long* lsum = acc + fcol;  // kLdsSums: [kFoldLane][256]
   if constexpr (kLdsSums)
 #pragma unroll
-    for (int k = 0; k < kLane; ++k) lsum[k * 256 + threadIdx.x] = 0;
+    for (int k = 0; k < kFoldLane; ++k) lsum[k * 256 + threadIdx.x] = 0;
   if (blockIdx.x == 0) {
     // clear this iteration's digit totals (the previous iteration's were consumed
     // by its finalisation, earlier on the stream)
@@ -333,118 +446,140 @@ __global__ __launch_bounds__(MAXT, (MAXT == 256 ? event_min_waves<PROC>() : 1)) 
   }
   __syncthreads();
 
-  LaneSums ls;
-  lane_sums_zero(ls);
+  long long ls[kFoldLane] = {0, 0, 0, 0, 0};
   // per-lane counts fit 32 bits (fewer than 2^31 events per launch), and so does the
   // event index: both keep registers free for the integrand
   unsigned long long wmax = 0ull;
   uint32_t nz = 0u, nnf = 0u;
   const int32_t step = static_cast<int32_t>(gridDim.x * blockDim.x);
   const int32_t nev32 = static_cast<int32_t>(a.nev);
-  for (int32_t i = static_cast<int32_t>(blockIdx.x * blockDim.x + threadIdx.x); i < nev32; i += step) {
-    double u[D > 0 ? D : VEGAS_MAX_DIM], x[D > 0 ? D : VEGAS_MAX_DIM];
-    // wave priorities: the uniforms (integer work) at the base priority, the grid map
-    // (the grid's LDS loads) one step up, the integrand at the top, so that a SIMD
-    // issues the floating-point work of waves already past their loads first and the
-    // waves of a block drift apart in phase (W+W- 340 against 366 us per 1e7-event
-    // launch, hadronic W+W- 490 against 532, with the fold there back at the base
-    // priority; the light W+ kernel is unchanged)
-    __builtin_amdgcn_s_setprio(0);
-    int bins[D > 0 ? D : VEGAS_MAX_DIM];
-    if constexpr (EXT) {
-#pragma unroll
-      for (int d = 0; d < (D > 0 ? D : VEGAS_MAX_DIM); ++d) {
-        if (d >= nd) break;
-        const double v = static_cast<double>(a.ext_y[static_cast<int64_t>(i) * nd + d]);
-        u[d] = fmin(fmax(v, kExtLo), kExtHi);
-      }
-    } else {
-      event_uniforms<D>(a.seed, a.iter, static_cast<uint64_t>(i), nd, u);
-      if constexpr (STRAT) {
-        uint32_t hc = a.s_cube ? static_cast<uint32_t>(a.s_cube[i]) : udiv(static_cast<uint32_t>(i), a.div_npc);
-        const uint32_t m = static_cast<uint32_t>(a.strata_m);
+  int32_t i = static_cast<int32_t>(blockIdx.x * blockDim.x + threadIdx.x);
+  // FUSED: at most kFoldEvents events of the block between two carries; `rest` is the
+  // distance to the end from the block's first event of the stretch (block-uniform)
+  const int32_t stretch = kFoldEvents / static_cast<int32_t>(blockDim.x);
+  int32_t rest = nev32 - static_cast<int32_t>(blockIdx.x * blockDim.x);
+  for (;;) {
+    for (int32_t pass = stretch; (!FUSED || pass > 0) && i < nev32; --pass, i += step) {
+      double u[D > 0 ? D : VEGAS_MAX_DIM], x[D > 0 ? D : VEGAS_MAX_DIM];
+      // wave priorities: the uniforms (integer work) at the base priority, the grid map
+      // (the grid's LDS loads) one step up, the integrand at the top, so that a SIMD
+      // issues the floating-point work of waves already past their loads first and the
+      // waves of a block drift apart in phase (W+W- 340 against 366 us per 1e7-event
+      // launch, hadronic W+W- 490 against 532, with the fold there back at the base
+      // priority; the light W+ kernel is unchanged)
+      __builtin_amdgcn_s_setprio(0);
+      int bins[D > 0 ? D : VEGAS_MAX_DIM];
+      if constexpr (EXT) {
 #pragma unroll
         for (int d = 0; d < (D > 0 ? D : VEGAS_MAX_DIM); ++d) {
           if (d >= nd) break;
-          const uint32_t q = udiv(hc, a.div_m);
-          u[d] = (static_cast<double>(hc - q * m) + u[d]) / a.strata_md;
-          hc = q;
+          const double v = static_cast<double>(a.ext_y[static_cast<int64_t>(i) * nd + d]);
+          u[d] = fmin(fmax(v, kExtLo), kExtHi);
+        }
+      } else {
+        event_uniforms<D>(a.seed, a.iter, static_cast<uint64_t>(i), nd, u);
+        if constexpr (STRAT) {
+          uint32_t hc = a.s_cube ? static_cast<uint32_t>(a.s_cube[i]) : udiv(static_cast<uint32_t>(i), a.div_npc);
+          const uint32_t m = static_cast<uint32_t>(a.strata_m);
+#pragma unroll
+          for (int d = 0; d < (D > 0 ? D : VEGAS_MAX_DIM); ++d) {
+            if (d >= nd) break;
+            const uint32_t q = udiv(hc, a.div_m);
+            u[d] = (static_cast<double>(hc - q * m) + u[d]) / a.strata_md;
+            hc = q;
+          }
+        }
+      }
+      __builtin_amdgcn_s_setprio(1);
+      const double J = grid_map<D>(e_lds, n, nd, u, x, bins);
+      __builtin_amdgcn_s_setprio(3);
+      // the bins, 4 of 8 bits per word.  With 10 or more fixed dimensions they are
+      // recorded before the integrand, so that only the packed words stay live across
+      // it (the fused fold takes the bins back out of them); with fewer, or a run-time
+      // dimension, keeping the bins themselves allocates better
+      constexpr int kWords = D > 0 ? (D + 3) / 4 : 4;
+      constexpr bool kEarlyBins = D >= 10;
+      uint32_t bw[kWords];
+      if constexpr (kEarlyBins) {
+#pragma unroll
+        for (int g = 0; g < kWords; ++g) {
+          bw[g] = 0u;
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (4 * g + j < nd) bw[g] |= static_cast<uint32_t>(bins[4 * g + j]) << (8 * j);
+          a.b.rec_bins[g * a.stride_rec + i] = bw[g];
+        }
+      }
+      double q;
+      const double f = integrand<PROC, PREC, D>(a.pc, x, q);
+      double w = J * f;
+      if constexpr (STRAT && !EXT)
+        if (a.s_cube) w *= a.s_N / (a.s_Hd * static_cast<double>(a.s_cnt[a.s_cube[i]]));
+      int obin = 0;
+      if constexpr (OBS) {
+        obin = obs_bin(obs_is_square<PROC>() ? sqrt(q) : q, a.obs_lo, a.obs_hi, a.obs_scale, a.nobs);
+        a.b.rec_obs[i] = static_cast<uint8_t>(obin);
+      }
+      if constexpr (EXT) w *= exp(-static_cast<double>(a.ext_lq[i]));
+      if (!isfinite(w * w)) {
+        ++nnf;
+        w = 0.0;
+      } else if (w != 0.0) {
+        ++nz;
+      }
+      a.b.rec_w[i] = w;
+      if constexpr (!kEarlyBins) {
+#pragma unroll
+        for (int g = 0; g < kWords; ++g) {
+          if (4 * g >= nd) break;
+          uint32_t word = 0;
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (4 * g + j < nd) word |= static_cast<uint32_t>(bins[4 * g + j]) << (8 * j);
+          a.b.rec_bins[g * a.stride_rec + i] = word;
+        }
+      }
+      if constexpr (PROC == VEGAS_WW_HAD) __builtin_amdgcn_s_setprio(0);
+      const unsigned long long wb = static_cast<unsigned long long>(__double_as_longlong(fabs(w)));
+      wmax = wb > wmax ? wb : wmax;
+      if constexpr (FUSED) {
+        if (w != 0.0) {
+          const FoldDigits g = fold_digits<PROC != VEGAS_GENZ>(w, E1, E2);
+          const long long t[kFoldLane] = {g.d[0], g.d[1], g.h[0], g.h[1], g.h[2]};
+#pragma unroll
+          for (int k = 0; k < kFoldLane; ++k) {
+            if (k == kFoldLane - 1 && !g.top) continue;
+            if constexpr (kLdsSums) lsum[k * 256 + threadIdx.x] += t[k];
+            else ls[k] += t[k];
+          }
+#pragma unroll
+          for (int d = 0; d < (D > 0 ? D : VEGAS_MAX_DIM); ++d) {
+            if (d >= nd) break;
+            const int bin = kEarlyBins ? static_cast<int>((bw[d >> 2] >> (8 * (d & 3))) & 0xffu) : bins[d];
+            fold_hist(acc, hist_col(d * n + bin), nslot, g);
+          }
+          if constexpr (OBS) fold_obs(acc, fcol_h + kLdsObs * obin, g);
         }
       }
     }
-    __builtin_amdgcn_s_setprio(1);
-    const double J = grid_map<D>(e_lds, n, nd, u, x, bins);
-    __builtin_amdgcn_s_setprio(3);
-    // the bins, 4 of 8 bits per word.  With 10 or more fixed dimensions they are
-    // recorded before the integrand, so that only the packed words stay live across
-    // it (the fused fold takes the bins back out of them); with fewer, or a run-time
-    // dimension, keeping the bins themselves allocates better
-    constexpr int kWords = D > 0 ? (D + 3) / 4 : 4;
-    constexpr bool kEarlyBins = D >= 10;
-    uint32_t bw[kWords];
-    if constexpr (kEarlyBins) {
-#pragma unroll
-      for (int g = 0; g < kWords; ++g) {
-        bw[g] = 0u;
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          if (4 * g + j < nd) bw[g] |= static_cast<uint32_t>(bins[4 * g + j]) << (8 * j);
-        a.b.rec_bins[g * a.stride_rec + i] = bw[g];
-      }
-    }
-    double q;
-    const double f = integrand<PROC, PREC, D>(a.pc, x, q);
-    double w = J * f;
-    if constexpr (STRAT && !EXT)
-      if (a.s_cube) w *= a.s_N / (a.s_Hd * static_cast<double>(a.s_cnt[a.s_cube[i]]));
-    int obin = 0;
-    if constexpr (OBS) {
-      obin = obs_bin(obs_is_square<PROC>() ? sqrt(q) : q, a.obs_lo, a.obs_hi, a.obs_scale, a.nobs);
-      a.b.rec_obs[i] = static_cast<uint8_t>(obin);
-    }
-    if constexpr (EXT) w *= exp(-static_cast<double>(a.ext_lq[i]));
-    if (!isfinite(w * w)) {
-      ++nnf;
-      w = 0.0;
-    } else if (w != 0.0) {
-      ++nz;
-    }
-    a.b.rec_w[i] = w;
-    if constexpr (!kEarlyBins) {
-#pragma unroll
-      for (int g = 0; g < kWords; ++g) {
-        if (4 * g >= nd) break;
-        uint32_t word = 0;
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          if (4 * g + j < nd) word |= static_cast<uint32_t>(bins[4 * g + j]) << (8 * j);
-        a.b.rec_bins[g * a.stride_rec + i] = word;
-      }
-    }
-    if constexpr (PROC == VEGAS_WW_HAD) __builtin_amdgcn_s_setprio(0);
-    const unsigned long long wb = static_cast<unsigned long long>(__double_as_longlong(fabs(w)));
-    wmax = wb > wmax ? wb : wmax;
+    if constexpr (!FUSED) break;
+    if (rest <= static_cast<int64_t>(stretch) * step) break;
+    rest -= stretch * step;
     if constexpr (FUSED) {
-      if (w != 0.0) {
-        EvDigits g;
-        if constexpr (kLdsSums) {
-          LaneSums t;
-          lane_sums_zero(t);
-          acc_sums<PROC != VEGAS_GENZ>(w, E1, E2, t, g);
+      if constexpr (kLdsSums)
 #pragma unroll
-          for (int k = 0; k < kLane; ++k) lsum[k * 256 + threadIdx.x] += t.v[k];
-        } else {
-          acc_sums<PROC != VEGAS_GENZ>(w, E1, E2, ls, g);
+        for (int k = 0; k < kFoldLane; ++k) {
+          ls[k] = lsum[k * 256 + threadIdx.x];
+          lsum[k * 256 + threadIdx.x] = 0;
         }
-        const bool top = top_digit_needed(g);
+      fold_sums_to_lds(ls, acc);
 #pragma unroll
-        for (int d = 0; d < (D > 0 ? D : VEGAS_MAX_DIM); ++d) {
-          if (d >= nd) break;
-          const int bin = kEarlyBins ? static_cast<int>((bw[d >> 2] >> (8 * (d & 3))) & 0xffu) : bins[d];
-          acc_hist(acc, hist_col(d * n + bin), nd * n, g, top);
-        }
-        if constexpr (OBS) acc_obs(acc, ncol_h + kObsW * obin, g, top);
-      }
+      for (int k = 0; k < kFoldLane; ++k) ls[k] = 0;
+      __syncthreads();
+      for (int q = threadIdx.x; q < nslot; q += blockDim.x) fold_carry(acc + hist_col(q), nslot);
+      if constexpr (OBS)
+        for (int q = threadIdx.x; q < 2 * (a.nobs + 2); q += blockDim.x) fold_carry(acc + fcol_h + 3 * q, 1);
+      __syncthreads();
     }
   }
   // block totals (LDS) -> one device-wide atomic per block and quantity
@@ -461,8 +596,8 @@ __global__ __launch_bounds__(MAXT, (MAXT == 256 ? event_min_waves<PROC>() : 1)) 
   }
   if constexpr (kLdsSums)
 #pragma unroll
-    for (int k = 0; k < kLane; ++k) ls.v[k] = lsum[k * 256 + threadIdx.x];
-  if constexpr (FUSED) acc_sums_to_lds(ls, acc);
+    for (int k = 0; k < kFoldLane; ++k) ls[k] = lsum[k * 256 + threadIdx.x];
+  if constexpr (FUSED) fold_sums_to_lds(ls, acc);
   __syncthreads();
   if (threadIdx.x == 0) {
     if (blk[0]) atomicMax(&a.b.maxw[0], blk[0]);
@@ -471,7 +606,21 @@ __global__ __launch_bounds__(MAXT, (MAXT == 256 ? event_min_waves<PROC>() : 1)) 
   }
   if constexpr (FUSED) {
     long long* row = a.b.part_acc + static_cast<int64_t>(blockIdx.x) * part_ld(ncol);
-    for (int i = threadIdx.x; i < ncol; i += blockDim.x) row[i] = acc[i];
+    if (threadIdx.x < kColHist) row[threadIdx.x] = acc[threadIdx.x];
+    for (int q = threadIdx.x; q < nslot; q += blockDim.x) {
+      const long long* c = acc + hist_col(q);
+      fold_row3(c[0], c[nslot], row + hist_col(q), nslot);
+      row[hist_col(q) + 3 * nslot] = c[2 * nslot];
+    }
+    if constexpr (OBS)
+      for (int q = threadIdx.x; q < a.nobs + 2; q += blockDim.x) {
+        const long long* c = acc + fcol_h + kLdsObs * q;
+        long long* r = row + ncol_h + kObsW * q;
+        fold_row3(c[0], c[1], r, 1);
+        r[2] += c[2] << 32;
+        fold_row3(c[3], c[4], r + kD1, 1);
+        r[kD1 + 3] = c[5];
+      }
   }
 }
 
@@ -1965,9 +2114,12 @@ void configure_lds(vegas_state* h) {
   h->acc_groups = (D + dpg - 1) / dpg;
   h->acc_lds = static_cast<int>(sizeof(long long) * (hist_cols(dpg * n) + ocol));
   const int full = static_cast<int>(sizeof(long long) * (hist_cols(D * n) + ocol));
-  // 10 or more dimensions: the lanes' S1, S2 digit sums also live in LDS ([7][256])
-  h->fused_lds = h->event_lds + full + (D >= 10 ? static_cast<int>(sizeof(long long) * kLane * 256) : 0);
-  h->fused_ok = h->fused_lds <= kFusedLdsMax;
+  // the fused fold is used where the finalisation can also re-fold in one block's LDS (the
+  // row's digits beside the grid); its own blocks need less: 48-bit digits and, with 10 or
+  // more dimensions, the lanes' sums ([5][256])
+  h->fused_ok = h->event_lds + full + (D >= 10 ? static_cast<int>(sizeof(long long) * kLane * 256) : 0) <= kFusedLdsMax;
+  h->fused_lds = h->event_lds + static_cast<int>(sizeof(long long) * (fold_cols(D * n) + fold_obs_cols(h->nobs) +
+                                                                      (D >= 10 ? kFoldLane * 256 : 0)));
   h->fin_lds = h->fused_ok ? full : 0;
   h->refine_lds = static_cast<int>(sizeof(double) * 4 * D * (n + 1));
   const int obs_lds = h->nobs ? static_cast<int>(sizeof(double) * 2 * (h->nobs + 2)) : 0;
