@@ -7,12 +7,27 @@
 // so only |M|^2 and the PDFs carry theta, and the pathwise gradient of the
 // estimator is (1/N) sum_i dw_i/dtheta.
 //
-// Work split: one wave owns a tile of 64 consecutive events.  Phase 1, lane =
-// event: the theta-independent part of the event (prefactor, m^2, angular factor,
-// log x sums) goes to LDS.  Phase 2, lane = parameter point: the lane walks the
-// tile's events in order, evaluates w and runs the reverse sweep, and keeps six
-// running sums.  Tile sums are then added by a fixed tree over tile index
-// (chunks of 256 tiles), so the result does not depend on the launch.
+// |M|^2 summed over flavours and helicities is, with s = m_ll^2, d = s - M_Z^2 and
+// D = d^2 + (M_Z G_Z)^2, proportional to c0 + (c1 s d + c2 s^2) / D, where c0 = 4 sum (Q_q
+// Q_l)^2 and c1, c2 are sums of the couplings of the point alone.  So the reverse sweep of
+// an event needs no sweep over the eight amplitudes: with K the theta-independent weight,
+// E = exp(a ln tau + b ln((1-x1)(1-x2))) and v = K E s / D, a point accumulates
+//   w = c0 K E + v (c1 d + c2 s),  v,  v d,  v s,  q = v (c1 d + c2 s) / D,  q d,
+//   w ln tau,  w ln((1-x1)(1-x2)),
+// and its derivatives are combinations of these sums with the point's constants, formed
+// once per row.
+//
+// Work split: one wave owns a row of consecutive 64-event tiles (rows from the number of
+// events alone).  Phase 1, lane = event: K, s and the two logarithms go to LDS.  Phase 2,
+// lane = (event group, parameter point): with B points the wave holds floor(64 / B)
+// groups, and group g takes events g, g + G, ... of the tile in order.  The groups' sums
+// are added in group order, the rows by a fixed tree, so the result does not depend on
+// the launch.
+//
+// Bound: FP64 VALU issue, 46 instructions per (event, point) instead of the 208 of a sweep
+// over the amplitudes with the library's exp: 64 points x 1e6 events 445 -> 136 us a call.
+// Few points: with one event at a time 9 of 64 lanes worked for 9 points; the groups take
+// the kernel from 61 to 12 us at 9 points x 1e5 events.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -25,18 +40,51 @@ constexpr int kGradMaxPoints = 64;
 constexpr int kGradVals = 6;  // w, dw/dMZ, dw/dGZ, dw/dsw2, dw/da, dw/db
 constexpr int kTreeRows = 256;
 
+// tiles per row of partials: at most 4096 rows, one for each wave of a full GPU (four waves
+// per SIMD on 256 CUs), as long as the tiles allow: one tile a row writes 48 MB of partials
+// for 64 points x 1e6 events, and each wave pays the couplings of its point once per row.
+// A function of the number of events alone.
+constexpr int64_t kGradRows = 4096;
+inline int64_t grad_tiles_per_row(int64_t ntiles) { return (ntiles + kGradRows - 1) / kGradRows; }
+
 struct GradArgs {
   PhysConst pc;          // nominal constants of the handle (mappings)
   const double* edges;   // grid [3][nbins+1]
   const double* theta;   // [B][5]
-  double* tiles;         // [ntiles][6][B]
+  double* rows_out;      // [nrows][6][B]
   uint64_t seed;
   int64_t nev;
-  int64_t ntiles;
+  int64_t ntiles, nrows, tiles_per_row;
   uint32_t iter;
   int nbins, B;
   double e4_12;          // e^4 / 12 (alpha fixed)
 };
+
+// a b + c with c in a scalar register pair as the instruction's operand (left to itself the
+// compiler copies each coefficient into the accumulating form's destination first)
+__device__ __forceinline__ double fma_coef(double a, double b, double c) {
+  double d;
+  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(c));
+  return d;
+}
+
+// exp(t) for |t| up to about 1e9 (0 and inf where it leaves the range): t = k ln 2 + r, ln 2
+// in two parts, exp(r) = 1 + r + r^2 q(r) with q the degree-9 interpolation at Chebyshev
+// nodes of |r| <= ln(2)/2 (1.6e-17 relative), then the exponent.  No branches; NaN stays NaN
+__device__ __forceinline__ double exp_core(double t) {
+  const double k = rint(t * 1.4426950408889634);
+  const double r = __fma_rn(-k, 2.3190468138462996e-17, __fma_rn(-k, 0.6931471805599453, t));
+  double q = fma_coef(2.510038549551032e-08, r, 2.7620088445409746e-07);
+  q = fma_coef(q, r, 2.7557268459997064e-06);
+  q = fma_coef(q, r, 2.4801521295954376e-05);
+  q = fma_coef(q, r, 0.00019841269863053618);
+  q = fma_coef(q, r, 0.0013888888917213717);
+  q = fma_coef(q, r, 0.008333333333330062);
+  q = fma_coef(q, r, 0.04166666666662413);
+  q = fma_coef(q, r, 0.16666666666666669);
+  q = fma_coef(q, r, 0.5000000000000001);
+  return ldexp(__fma_rn(r * r, q, r) + 1.0, static_cast<int>(k));
+}
 
 // Z couplings g_L = (T3 - Q x)/sqrt(x(1-x)), g_R = -Q sqrt(x/(1-x)), x = sin^2 theta_W,
 // and their derivatives in x
@@ -49,63 +97,92 @@ __device__ __forceinline__ void zcoup(double T3, double Q, double x, double& gL,
   dgR = -Q / (2.0 * sqrt(x) * (1.0 - x) * sqrt(1.0 - x));
 }
 
-__global__ __launch_bounds__(256) void k_dy_grad(GradArgs a) {
+// phase 2 of one tile: lane's events e = g, g + G, ... (row 64 is a row of weight 0)
+template <bool FAST>
+__device__ __forceinline__ void grad_points(const double* ev, int g, int G, double M2, double MG2, double pa, double pb,
+                                            double c0, double c1, double c2, double S[8]) {
+  for (int e0 = 0; e0 < 64; e0 += G) {
+    const double* r = ev + 4 * (e0 + g < 64 ? e0 + g : 64);
+    const double K = r[0], s = r[1], ls = r[2], Ls = r[3];
+    const double t = __fma_rn(pa, ls, pb * Ls);
+    const double KE = K * (FAST ? exp_core(t) : exp(t));
+    const double d = s - M2, iD = rcp_nr(__fma_rn(d, d, MG2));
+    const double v = KE * iD * s, f = __fma_rn(c1, d, c2 * s);
+    const double vf = v * f, w = __fma_rn(c0, KE, vf), q = vf * iD;
+    S[0] += w;
+    S[1] += v;
+    S[2] = __fma_rn(v, d, S[2]);
+    S[3] = __fma_rn(v, s, S[3]);
+    S[4] += q;
+    S[5] = __fma_rn(q, d, S[5]);
+    S[6] = __fma_rn(w, ls, S[6]);
+    S[7] = __fma_rn(w, Ls, S[7]);
+  }
+}
+
+constexpr int kGradSums = 8;
+constexpr int kGradLds = 65 * 4 + kGradSums * 64;  // doubles of LDS per wave: the tile's rows, the groups' sums
+
+__global__ __launch_bounds__(256, 4) void k_dy_grad(GradArgs a) {
   extern __shared__ double sm[];
   const int n = a.nbins;
   double* e_lds = sm;                                    // [3][n+1]
-  double* evs = sm + 3 * (n + 1);                        // [4 waves][64 events][5]
-  for (int i = threadIdx.x; i < 3 * (n + 1); i += blockDim.x) e_lds[i] = a.edges[i];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int wpb = blockDim.x >> 6;
-  double* ev = evs + wave * 64 * 5;
+  double* ev = sm + 3 * (n + 1) + wave * kGradLds;       // [65][4]
+  double* gs = ev + 65 * 4;                              // [8][64]
+  for (int i = threadIdx.x; i < 3 * (n + 1); i += blockDim.x) e_lds[i] = a.edges[i];
+  if (lane < 4) ev[64 * 4 + lane] = lane == 1 ? -1.0 : 0.0;
 
-  // this lane's parameter point (phase 2): couplings and their sw2-derivatives
-  double M = 0, G = 0, x = 0.25, pa = 0, pb = 0;
-  if (lane < a.B) {
-    M = a.theta[5 * lane + 0];
-    G = a.theta[5 * lane + 1];
-    x = a.theta[5 * lane + 2];
-    pa = a.theta[5 * lane + 3];
-    pb = a.theta[5 * lane + 4];
-  }
-  double gg[2][4], dgg[2][4];
+  // this lane's group and parameter point: couplings and their sw2-derivatives
+  const int G = 64 / a.B, g = lane / a.B, b = lane - g * a.B;
+  const bool mine = g < G;
+  const double* th = a.theta + 5 * (mine ? b : 0);
+  const double M = th[0], GZ = th[1], x = th[2], pa = th[3], pb = th[4];
+  // exp_core's range: ln tau and the clamped logarithm are at most 1e4 in size
+  const bool fast = __all(fabs(pa) <= 1e4 && fabs(pb) <= 1e4);
+  double c0 = 0.0, c1 = 0.0, c2 = 0.0, dc1 = 0.0, dc2 = 0.0;
   {
     double lL, lR, dlL, dlR;
     zcoup(-0.5, -1.0, x, lL, lR, dlL, dlR);
     const double gl[2] = {lL, lR}, dgl[2] = {dlL, dlR};
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
+      const double qql = q == 0 ? -2.0 / 3.0 : 1.0 / 3.0;  // Q_q Q_l, Q_l = -1
       double qL, qR, dqL, dqR;
       zcoup(q == 0 ? 0.5 : -0.5, q == 0 ? 2.0 / 3.0 : -1.0 / 3.0, x, qL, qR, dqL, dqR);
       const double gq[2] = {qL, qR}, dgq[2] = {dqL, dqR};
+      c0 += 4.0 * qql * qql;
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
         for (int hp = 0; hp < 2; ++hp) {
-          gg[q][2 * h + hp] = gq[h] * gl[hp];
-          dgg[q][2 * h + hp] = dgq[h] * gl[hp] + gq[h] * dgl[hp];
+          const double gg = gq[h] * gl[hp], dgg = dgq[h] * gl[hp] + gq[h] * dgl[hp];
+          c1 += 2.0 * qql * gg;
+          dc1 += 2.0 * qql * dgg;
+          c2 += gg * gg;
+          dc2 += 2.0 * gg * dgg;
         }
     }
   }
-  const double qql[2] = {-2.0 / 3.0, 1.0 / 3.0};  // Q_q Q_l, Q_l = -1
-  const double pdfA2 = a.pc.pdfA * a.pc.pdfA;
+  const double M2 = M * M, MG2 = (M * GZ) * (M * GZ);
+  const double kc = a.pc.conv * a.pc.pdfA * a.pc.pdfA * a.e4_12;
   __syncthreads();
 
-  const int64_t groups = (a.ntiles + wpb - 1) / wpb;
-  for (int64_t grp = blockIdx.x; grp < groups; grp += gridDim.x) {
-    const int64_t tile = grp * wpb + wave;
-    const bool tile_ok = tile < a.ntiles;
-    // wave priorities: phase 1 (uniforms, grid map, kinematics) at the base priority,
-    // phase 2 (the parameter points' sums) raised, so that waves of a block drift apart
-    // in phase (measured 1.7 % faster than equal priorities)
-    __builtin_amdgcn_s_setprio(0);
-    // ---- phase 1: lane = event, theta-independent part at the nominal proposal
-    if (tile_ok) {
+  for (int64_t row = static_cast<int64_t>(blockIdx.x) * wpb + wave; row < a.nrows;
+       row += static_cast<int64_t>(gridDim.x) * wpb) {
+    const int64_t t1 = min(a.ntiles, (row + 1) * a.tiles_per_row);
+    double S[kGradSums] = {0, 0, 0, 0, 0, 0, 0, 0};
+    for (int64_t tile = row * a.tiles_per_row; tile < t1; ++tile) {
+      // wave priorities: phase 1 (uniforms, grid map, kinematics) at the base priority,
+      // phase 2 (the parameter points' sums) raised, so that the waves of a SIMD drift
+      // apart in phase
+      __builtin_amdgcn_s_setprio(0);
+      // ---- phase 1: lane = event, theta-independent part at the nominal proposal
       const int64_t i = tile * 64 + lane;
-      double P = 0.0, m2 = 1.0, ang = 0.0, ls = 0.0, Ls = 0.0;
+      double K = 0.0, m2 = -1.0, ls = 0.0, Ls = 0.0;
       if (i < a.nev) {
         double u[3], xx[3];
-        int bins[3];
         event_uniforms<3>(a.seed, a.iter, static_cast<uint64_t>(i), 3, u);
         double J = 1.0;
         {
@@ -121,97 +198,67 @@ __global__ __launch_bounds__(256) void k_dy_grad(GradArgs a) {
             const double h = e[k + 1] - e[k];
             xx[d] = __fma_rn(delta, h, e[k]);
             J *= dn * h;
-            bins[d] = k;
           }
         }
         double jbw;
-        m2 = bw_map(a.pc, xx[0], a.pc.rho_rng, jbw);
+        const double s = bw_map(a.pc, xx[0], a.pc.rho_rng, jbw);
         double L, l1, l2;
         {
 #pragma clang fp contract(off)
-          L = log(m2 * a.pc.invS);
+          L = log(s * a.pc.invS);
           l1 = xx[1] * L;
           l2 = L - l1;
         }
         const double jtau = -L * a.pc.invS;
         const double cs = 2.0 * xx[2] - 1.0;
-        P = a.pc.conv * J * jbw * jtau * 2.0 * (0.5 / m2) * (1.0 / (16.0 * kPi));
-        ang = 2.0 * (1.0 + cs * cs);
-        ls = L;
-        Ls = log(expm1(l1) * expm1(l2));
+        // conv J_grid J_bw J_tau 2 / (2 s) / (16 pi) times e^4 / 12 s^2 2 (1 + cos^2) / s^2
+        K = kc * J * jbw * jtau * (2.0 / s) * (1.0 / (16.0 * kPi)) * (1.0 + cs * cs);
+        if (K != 0.0) {
+          m2 = s;
+          ls = L;
+          Ls = fmax(log(expm1(l1) * expm1(l2)), -1e4);
+        }
       }
-      ev[lane * 5 + 0] = P;
-      ev[lane * 5 + 1] = m2;
-      ev[lane * 5 + 2] = ang;
-      ev[lane * 5 + 3] = ls;
-      ev[lane * 5 + 4] = Ls;
+      ev[lane * 4 + 0] = K;
+      ev[lane * 4 + 1] = m2;
+      ev[lane * 4 + 2] = ls;
+      ev[lane * 4 + 3] = Ls;
+      // the wave reads what its own lanes wrote (LDS operations of a wave are in order)
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      __builtin_amdgcn_s_setprio(3);
+      // ---- phase 2: lane = (event group, parameter point)
+      if (fast) grad_points<true>(ev, mine ? g : 0, G, M2, MG2, pa, pb, c0, c1, c2, S);
+      else grad_points<false>(ev, mine ? g : 0, G, M2, MG2, pa, pb, c0, c1, c2, S);
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
-    __syncthreads();
-    __builtin_amdgcn_s_setprio(3);
-    // ---- phase 2: lane = parameter point, events of the tile in order
-    if (tile_ok && lane < a.B) {
-      double S[kGradVals] = {0, 0, 0, 0, 0, 0};
-      const double MG = M * G;
-      for (int e = 0; e < 64; ++e) {
-        const double P = ev[e * 5 + 0];
-        if (P == 0.0) continue;
-        const double m2 = ev[e * 5 + 1], ang = ev[e * 5 + 2], ls = ev[e * 5 + 3], Ls = ev[e * 5 + 4];
-        // forward
-        const double ds = m2 - M * M;
-        const double Den = ds * ds + MG * MG;
-        const double iD = 1.0 / Den;
-        const double pre = ds * iD, pim = -MG * iD;
-        const double invs = 1.0 / m2;
-        double sumA = 0.0;
+    // the groups' sums in group order
+    if (G > 1) {
 #pragma unroll
-        for (int q = 0; q < 2; ++q)
+      for (int k = 0; k < kGradSums; ++k) gs[k * 64 + lane] = S[k];
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      if (lane < a.B)
+        for (int gg = 1; gg < G; ++gg)
 #pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            const double re = qql[q] * invs + gg[q][t] * pre;
-            const double im = gg[q][t] * pim;
-            sumA += re * re + im * im;
-          }
-        const double mef = a.e4_12 * m2 * m2 * ang;
-        const double ME = mef * sumA;
-        const double ff = pdfA2 * exp(pa * ls + pb * Ls);
-        const double w = P * ff * ME;
-        // reverse sweep, seeded with dw/dw = 1
-        const double ME_bar = P * ff;
-        const double ff_bar = P * ME;
-        const double a_bar = ff_bar * ff * ls;
-        const double b_bar = ff_bar * ff * Ls;
-        const double sumA_bar = ME_bar * mef;
-        double pre_bar = 0.0, pim_bar = 0.0, x_bar = 0.0;
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-#pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            const double re = qql[q] * invs + gg[q][t] * pre;
-            const double im = gg[q][t] * pim;
-            const double re_bar = 2.0 * re * sumA_bar, im_bar = 2.0 * im * sumA_bar;
-            pre_bar += re_bar * gg[q][t];
-            pim_bar += im_bar * gg[q][t];
-            x_bar += (re_bar * pre + im_bar * pim) * dgg[q][t];
-          }
-        double ds_bar = pre_bar * iD;
-        const double iD_bar = pre_bar * ds - pim_bar * MG;
-        double MG_bar = -pim_bar * iD;
-        const double Den_bar = -iD_bar * iD * iD;
-        ds_bar += Den_bar * 2.0 * ds;
-        MG_bar += Den_bar * 2.0 * MG;
-        const double M_bar = ds_bar * (-2.0 * M) + MG_bar * G;
-        const double G_bar = MG_bar * M;
-        S[0] += w;
-        S[1] += M_bar;
-        S[2] += G_bar;
-        S[3] += x_bar;
-        S[4] += a_bar;
-        S[5] += b_bar;
-      }
-#pragma unroll
-      for (int k = 0; k < kGradVals; ++k) a.tiles[(tile * kGradVals + k) * a.B + lane] = S[k];
+          for (int k = 0; k < kGradSums; ++k) S[k] += gs[k * 64 + gg * a.B + lane];
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
-    __syncthreads();
+    if (lane < a.B) {
+      double* o = a.rows_out + row * kGradVals * a.B + lane;
+      o[0] = S[0];
+      o[a.B] = -2.0 * M * (c1 * S[1] + GZ * GZ * S[4] - 2.0 * S[5]);
+      o[2 * a.B] = -2.0 * M2 * GZ * S[4];
+      o[3 * a.B] = dc1 * S[2] + dc2 * S[3];
+      o[4 * a.B] = S[6];
+      o[5 * a.B] = S[7];
+    }
   }
 }
 
@@ -245,13 +292,21 @@ __global__ __launch_bounds__(256) void k_tree_level(const double* in, double* ou
   }
 }
 
-// final row (6 x B sums) -> sigma[B], dsigma[B][5]
-__global__ void k_grad_out(const double* tot, int B, int64_t nev, double* sigma, double* dsigma) {
-  const int b = threadIdx.x;
-  if (b >= B) return;
-  const double iN = 1.0 / static_cast<double>(nev);
-  sigma[b] = tot[0 * B + b] * iN;
-  for (int k = 0; k < 5; ++k) dsigma[5 * b + k] = tot[(1 + k) * B + b] * iN;
+// the tree's last rows (at most kGradLast) added in order -> sigma[B], dsigma[B][5]
+constexpr int kGradLast = 16;
+__global__ __launch_bounds__(384) void k_grad_out(const double* in, int64_t rows, int B, int64_t nev, double* sigma,
+                                                  double* dsigma) {
+  const int c = threadIdx.x, cols = kGradVals * B;
+  if (c >= cols) return;
+  double v[kGradLast], t = 0.0;
+#pragma unroll
+  for (int r = 0; r < kGradLast; ++r) v[r] = r < rows ? in[r * cols + c] : 0.0;
+#pragma unroll
+  for (int r = 0; r < kGradLast; ++r) t += v[r];
+  t *= 1.0 / static_cast<double>(nev);
+  const int k = c / B, b = c - k * B;
+  if (k == 0) sigma[b] = t;
+  else dsigma[5 * b + k - 1] = t;
 }
 
 }  // namespace vg

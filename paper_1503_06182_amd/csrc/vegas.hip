@@ -2867,8 +2867,9 @@ int vegas_get_weights(vegas_handle h, int64_t first, int64_t n, double* w, uint8
 }
 
 namespace {
-// doubles of adjoint scratch a call needs: the per-tile partials ([ceil(n/64)][6][B]) and
-// the first level of the fixed tree over them
+// doubles of adjoint scratch a call may ask for: a row of partials per 64-event tile
+// ([ceil(n/64)][6][B]) and the first level of the fixed tree over them -- the documented
+// size; rows of several tiles need less of it
 size_t grad_scratch_doubles(int32_t B, int64_t n_events) {
   const int64_t ntiles = (n_events + 63) / 64;
   const int64_t lvl1 = (ntiles + kTreeRows - 1) / kTreeRows;
@@ -2888,16 +2889,16 @@ int grad_launch(vegas_handle h, const double* params_dev, int32_t B, int64_t n_e
                 double* sigma_dev, double* dsigma_dev, double* buf) {
   const int64_t ntiles = (n_events + 63) / 64;
   const int cols = kGradVals * B;
-  double* tiles = buf;
-  double* lvl = buf + ntiles * cols;
   GradArgs ga;
   ga.pc = h->pc;
   ga.edges = h->b.edges;
   ga.theta = params_dev;
-  ga.tiles = tiles;
+  ga.rows_out = buf;
   ga.seed = h->cfg.seed;
   ga.nev = n_events;
   ga.ntiles = ntiles;
+  ga.tiles_per_row = grad_tiles_per_row(ntiles);
+  ga.nrows = (ntiles + ga.tiles_per_row - 1) / ga.tiles_per_row;
   ga.iter = iteration;
   ga.nbins = h->n;
   ga.B = B;
@@ -2905,39 +2906,34 @@ int grad_launch(vegas_handle h, const double* params_dev, int32_t B, int64_t n_e
     const double e2 = 4.0 * kPi * h->params[VEGAS_P_ALPHA];
     ga.e4_12 = e2 * e2 / 12.0;
   }
-  const int lds = static_cast<int>(sizeof(double) * (3 * (h->n + 1) + 4 * 64 * 5));
-  const int64_t groups = (ntiles + 3) / 4;
-  int occ = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, reinterpret_cast<const void*>(&k_dy_grad), 256, lds) !=
-          hipSuccess || occ < 1)
-    occ = 1;
-  int64_t blocks = static_cast<int64_t>(h->ncu) * occ;
-  if (blocks > groups) blocks = groups;
+  const int lds = static_cast<int>(sizeof(double) * (3 * (h->n + 1) + 4 * kGradLds));
+  const int64_t blocks = (ga.nrows + 3) / 4;  // one row per wave: at most kGradRows / 4
   {
     TimedLaunch t(h, 0);  // timed as the events stage
     hipExtLaunchKernelGGL(k_dy_grad, dim3(static_cast<unsigned>(blocks)), dim3(256), lds, h->stream, t.e0, t.e1, 0,
                           ga);
     VG_HIP(t.done());
   }
-  // fixed tree over tiles: 256-row chunks, level by level, ping-pong between the buffers
-  const double* in = tiles;
-  double* out = lvl;
-  int64_t rows = ntiles;
-  while (rows > 1) {
+  // fixed tree over the rows: one level of 256-row chunks leaves at most kGradLast, which
+  // the output kernel adds (kGradRows bounds the rows)
+  static_assert((kGradRows + kTreeRows - 1) / kTreeRows <= kGradLast, "one level must leave few enough rows");
+  const double* in = buf;
+  int64_t rows = ga.nrows;
+  if (rows > kGradLast) {
+    double* lvl = buf + rows * cols;
     const int64_t rout = (rows + kTreeRows - 1) / kTreeRows;
-    const int tiles_c = (cols + kTreeCols - 1) / kTreeCols, gy = tiles_c < 64 ? tiles_c : 64;
+    const int tiles_c = (cols + kTreeCols - 1) / kTreeCols;
     TimedLaunch t(h, 1);  // timed as the fold stage
-    hipExtLaunchKernelGGL(k_tree_level, dim3(static_cast<unsigned>(rout), gy), dim3(kTreeRows), 0, h->stream, t.e0,
-                          t.e1, 0, in, out, rows, cols);
+    hipExtLaunchKernelGGL(k_tree_level, dim3(static_cast<unsigned>(rout), tiles_c), dim3(kTreeRows), 0, h->stream, t.e0,
+                          t.e1, 0, in, lvl, rows, cols);
     VG_HIP(t.done());
     rows = rout;
-    in = out;
-    out = (out == lvl) ? tiles : lvl;
+    in = lvl;
   }
   {
     TimedLaunch t(h, 2);  // timed as the finalisation stage
-    hipExtLaunchKernelGGL(k_grad_out, dim3(1), dim3(64), 0, h->stream, t.e0, t.e1, 0, in, B, n_events, sigma_dev,
-                          dsigma_dev);
+    hipExtLaunchKernelGGL(k_grad_out, dim3(1), dim3(384), 0, h->stream, t.e0, t.e1, 0, in, rows, B, n_events,
+                          sigma_dev, dsigma_dev);
     VG_HIP(t.done());
   }
   return VEGAS_OK;
