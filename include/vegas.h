@@ -378,8 +378,10 @@ typedef struct vegas_flow_state *vegas_flow;
  * keyed by seed, zero output layer (the identity map, q = 1).  max_batch
  * (1 .. 2^22) bounds the batch of the density / training calls; max_sample
  * (0 .. 2^31-1) the events of a flow iteration.  The library allocates
- * about 3.4 KB per batch event plus 36 B per sample event plus 5 MB of
- * device memory, freed by vegas_flow_destroy.  stream: hipStream_t or NULL.
+ * about 3.4 KB per batch event (for each of the first 16,384 of them 19 KB, a batch
+ * of that size running all layers at once) plus 36 B per sample event plus 5 MB plus
+ * 1 MB per 256 batch events (64 MB at most) of device memory, freed by
+ * vegas_flow_destroy.  stream: hipStream_t or NULL.
  * Errors: VEGAS_EINVAL, VEGAS_ENOMEM, VEGAS_EHIP. */
 int vegas_flow_create(int32_t max_batch, int64_t max_sample, uint64_t seed, void *stream, vegas_flow *out);
 int vegas_flow_destroy(vegas_flow f);

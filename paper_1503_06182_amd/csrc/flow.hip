@@ -1,15 +1,19 @@
 // flow.hip -- kernels and C ABI of the learned proposal (see flow.hpp).
 //
 // Training step on a batch of VEGAS-weighted events (y_i, w_i), loss
-// L = -sum_i w_i log q(y_i) / sum_i w_i (importance-weighted forward KL):
-//   gather (a per-step bijection of the data indices), per-layer forward in the
-//   density direction (activations of every layer kept), the per-event loss
-//   seeds dL/dlog q_i = -w_i / sum w, per-layer backward (spline reverse sweep,
-//   MLP backward on MFMA), weight gradients as MFMA contractions over the
-//   batch, Adam on the FP32 master weights, BF16 copies refreshed.
+// L = -sum_i w_i log q(y_i) / sum_i w_i (importance-weighted forward KL), in four launches:
+//   k_flow_wsum   sum w over the batch (a per-step bijection of the data indices)
+//   k_flow_events each block takes 16 events through the six layers in the density
+//                 direction and back (spline reverse sweeps, MLP backward on MFMA; the
+//                 per-event loss seeds are dL/dlog q_i = -w_i / sum w)
+//   k_flow_wgrad_part  weight gradients as MFMA contractions over the batch, all layers
+//   k_flow_wgrad_sum   adds the parts; Adam on the FP32 master weights; BF16 copies
+// Batches above kFusedBatch keep one layer's gradients at a time and run layer by layer
+// (k_flow_layer, k_flow_layer_bwd), the same arithmetic.
 // Sampling: z uniform (Philox) -> inverse layers 5..0 -> y, log q(y).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <string>
@@ -302,19 +306,28 @@ __global__ __launch_bounds__(256, 3) void k_flow_layer(const float* __restrict__
 }
 
 // ---------------------------------------------------------------------------
-// backward of one layer over a batch (one 32-event tile per block iteration)
-//   gout = dL/d(layer output) [B][8], glq = dL/d log q [B]  ->  gin = dL/d(layer input);
-//   stores H1, H2, DR (bf16 and fp32), DH2 (bf16 and fp32), DH1 (fp32), COND for the weight
-//   gradients, feature-major ([feature][ld], ld = the batch capacity rounded up to 32) so
-//   the contractions over events read contiguous runs; every row of the last tile is
-//   written, and the rows past the batch carry zero gradients
+// operands of the weight gradients: per layer and group of 32 events, feature-major --
+// element (layer, event, feature) of an array with F features at
+// ((layer groups + event / 32) F + feature) 32 + event % 32 -- so that the contractions over
+// events read whole kilobytes and a tile of 16 or 32 events writes 32 or 64 bytes of a
+// feature at once.  Rows past the batch (to a multiple of 32) carry zero gradients.
 // ---------------------------------------------------------------------------
 struct FlowBwdBufs {
   uint16_t *H1, *H2, *DRb, *DH2b;
   float *DRf, *DH2f, *DH1f, *COND;
-  int64_t ld;
+  int64_t groups;  // groups of 32 events per layer
 };
 
+__device__ __forceinline__ int64_t bwd_at(const FlowBwdBufs& s, int slot, int64_t ev, int F, int feature) {
+  return ((slot * s.groups + (ev >> 5)) * F + feature) * 32 + (ev & 31);
+}
+
+// ---------------------------------------------------------------------------
+// backward of one layer over a batch (one 32-event tile per block iteration)
+//   gout = dL/d(layer output) [B][8], glq = dL/d log q [B]  ->  gin = dL/d(layer input);
+//   stores H1, H2, DR (bf16 and fp32), DH2 (bf16 and fp32), DH1 (fp32), COND in slot 0 of the
+//   weight gradients' operands; every row of the last tile is written
+// ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_flow_layer_bwd(const float* __restrict__ master,
                                                          const uint16_t* __restrict__ wb, int l,
                                                          const float* __restrict__ vin, const float* __restrict__ gout,
@@ -334,15 +347,15 @@ __global__ __launch_bounds__(256) void k_flow_layer_bwd(const float* __restrict_
       const int64_t ev = e0 + e;
       const float v = ev < B ? vin[ev * FL_NDIM + kFlowC[l][c]] : 0.5f;
       cond[e][c] = v;
-      s.COND[c * s.ld + ev] = v;
+      s.COND[bwd_at(s, 0, ev, 4, c)] = v;
     }
     __syncthreads();
     mlp_tile32(m, w, cond, h1, h2, par);
     // activations of the tile for the weight gradients
     for (int i = tid; i < FL_TILE * FL_HID; i += blockDim.x) {
       const int e = i % FL_TILE, j = i / FL_TILE;
-      s.H1[j * s.ld + e0 + e] = h1[e * FL_LDA + j];
-      s.H2[j * s.ld + e0 + e] = h2[e * FL_LDA + j];
+      s.H1[bwd_at(s, 0, e0 + e, FL_HID, j)] = h1[e * FL_LDA + j];
+      s.H2[bwd_at(s, 0, e0 + e, FL_HID, j)] = h2[e * FL_LDA + j];
     }
     // spline reverse sweep: thread (event, transformed coordinate)
     if (tid < FL_TILE * 4) {
@@ -374,8 +387,8 @@ __global__ __launch_bounds__(256) void k_flow_layer_bwd(const float* __restrict_
       const int e = i % FL_TILE, c = i / FL_TILE;
       const float g = par[e * FL_LDP + c];
       dpb[e * FL_LDP + c] = f2bf(g);
-      s.DRb[c * s.ld + e0 + e] = f2bf(g);
-      s.DRf[c * s.ld + e0 + e] = g;
+      s.DRb[bwd_at(s, 0, e0 + e, FL_NOUTP, c)] = f2bf(g);
+      s.DRf[bwd_at(s, 0, e0 + e, FL_NOUTP, c)] = g;
     }
     __syncthreads();
     // dh2 = dp W3^T (mask h2 > 0): A = dpb [32][192], Bt = W3n [128 in][192 out]
@@ -400,8 +413,8 @@ __global__ __launch_bounds__(256) void k_flow_layer_bwd(const float* __restrict_
           const int row = rb * 16 + 4 * (lane >> 4) + j;
           const float g = dh2v[rb][cc][j];
           dpb[row * FL_LDA + col] = f2bf(g);
-          s.DH2b[col * s.ld + e0 + row] = f2bf(g);
-          s.DH2f[col * s.ld + e0 + row] = g;
+          s.DH2b[bwd_at(s, 0, e0 + row, FL_HID, col)] = f2bf(g);
+          s.DH2f[bwd_at(s, 0, e0 + row, FL_HID, col)] = g;
         }
       }
     __syncthreads();
@@ -416,7 +429,7 @@ __global__ __launch_bounds__(256) void k_flow_layer_bwd(const float* __restrict_
           const int row = rb * 16 + 4 * (lane >> 4) + j;
           const float g = bf2f(h1[row * FL_LDA + col]) > 0.f ? acc[j] : 0.f;
           par[row * FL_LDP + col] = g;
-          s.DH1f[col * s.ld + e0 + row] = g;
+          s.DH1f[bwd_at(s, 0, e0 + row, FL_HID, col)] = g;
         }
       }
     __syncthreads();
@@ -435,128 +448,533 @@ __global__ __launch_bounds__(256) void k_flow_layer_bwd(const float* __restrict_
   }
 }
 
+// the data index of batch position i: the whole data in order (n == 0), or the bijection
+// j -> (a j + c) mod n of the epoch (a, j, c < n < 2^31: no overflow)
+struct BatchIdx {
+  uint64_t n, a, c, start, magic;  // magic = floor((2^64 - 1) / n)
+};
+// x mod n for x < 2^63: the quotient by the reciprocal is at most 2 short
+__device__ __forceinline__ uint64_t mod_magic(uint64_t x, uint64_t n, uint64_t magic) {
+  uint64_t r = x - __umul64hi(x, magic) * n;
+  r = r >= n ? r - n : r;
+  return r >= n ? r - n : r;
+}
+__device__ __forceinline__ int64_t batch_at(const BatchIdx& x, int64_t i) {
+  if (x.n == 0) return i;
+  const uint64_t j = mod_magic(x.start + static_cast<uint64_t>(i), x.n, x.magic);
+  return static_cast<int64_t>(mod_magic(x.a * j + x.c, x.n, x.magic));
+}
+
 // ---------------------------------------------------------------------------
-// weight gradients of one layer, split over the batch (split-K): split sp sums the
+// the six layers of 16 events per block (4 waves) in the density direction, and with BWD
+// the backward through them: activations stay in LDS (the spline parameters of all six
+// layers, binary16) and registers (the ReLU masks), so nothing is recomputed and a step has
+// no launch per layer.  Every value is formed by the operations of k_flow_layer<false> and
+// k_flow_layer_bwd in their order: the same bits.
+//
+// Bound by latency: 16 events (the matrix instructions' tile) give a batch of 4096 one block
+// per CU; a layer's splines run on one wave while the others store the weight gradients'
+// operands, and each phase's weights are loaded before the spline or product that precedes
+// it.  4096 events: 68 us for the twelve launches' 195 (and the copies, fills and gaps between
+// them); a step of 32 launches took 366 us, its four launches take 116.
+// ---------------------------------------------------------------------------
+constexpr int kEvTile = 16;
+constexpr int kWgSplit = 256;  // events per split of the weight gradients (more above kFusedBatch)
+constexpr int64_t kFusedBatch = 16384;  // above: one layer's operands at a time (17 KB per event for all six)
+
+template <int KS>
+struct WFrags {  // two 16-column blocks of a wave, KS steps of 32
+  bf16x8_t f[2][KS];
+};
+template <int KS>
+__device__ __forceinline__ void load_wfrags(WFrags<KS>& o, const uint16_t* __restrict__ Bt, int ldb, int wave, int lane) {
+#pragma unroll
+  for (int cc = 0; cc < 2; ++cc)
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) o.f[cc][ks] = load_bfrag(Bt, ldb, (2 * wave + cc) * 16, ks * 32, lane);
+}
+
+template <bool BWD>
+__global__ __launch_bounds__(256) void k_flow_events(const float* __restrict__ master, const uint16_t* __restrict__ wb,
+                                                     const float* __restrict__ y, const double* __restrict__ w,
+                                                     BatchIdx bx, const double* __restrict__ scal, float* logq,
+                                                     int64_t B, FlowBwdBufs s) {
+  __shared__ float v[kEvTile][FL_NDIM], vin[BWD ? FL_NLAYER : 1][kEvTile][4];  // current point; transformed inputs
+  __shared__ float cond[kEvTile][4];
+  __shared__ float g[kEvTile][FL_NDIM];
+  __shared__ __align__(16) _Float16 par[BWD ? FL_NLAYER : 1][kEvTile * FL_LDQ];
+  __shared__ __align__(16) uint16_t h1[kEvTile * FL_LDA], h2[kEvTile * FL_LDA];
+  __shared__ __align__(16) float gp[BWD ? kEvTile * FL_LDP : 1];      // gradients of the spline parameters, then dh1
+  __shared__ __align__(16) uint16_t gb[BWD ? kEvTile * FL_LDP : 1];   // their bf16, then dh2's
+  __shared__ __align__(16) float w1[BWD ? 4 * FL_HID : 1];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int ri = lane & 15, kq = 4 * (lane >> 4), kq8 = 8 * (lane >> 4);
+  const int64_t e0 = static_cast<int64_t>(blockIdx.x) * kEvTile;
+  // thread (event, slot) of the splines: wave 0
+  const int se = (tid >> 2) & (kEvTile - 1), sc = tid & 3;
+  const int64_t sev = e0 + se;
+  const bool spl = tid < 4 * kEvTile;
+  double wev = 0.0;
+  if (tid < kEvTile * FL_NDIM) {
+    const int e = tid >> 3, d = tid & 7;
+    v[e][d] = e0 + e < B ? y[batch_at(bx, e0 + e) * FL_NDIM + d] : 0.5f;
+    if (BWD) g[e][d] = 0.f;
+  }
+  if (BWD && spl && sev < B) wev = w[batch_at(bx, sev)];
+  float lq = 0.f;
+  uint64_t m1 = 0, m2 = 0;  // ReLU masks of this lane's elements of dh1, dh2: bit 8 l + 4 cc + j
+  for (int l = 0; l < FL_NLAYER; ++l) {
+    const float* m = master + l * FL_LAYER;
+    const uint16_t* wl = wb + static_cast<int64_t>(l) * FB_LAYER;
+    WFrags<FL_HID / 32> b2;
+    load_wfrags(b2, wl + FB_W2T, FL_HID, wave, lane);
+    bf16x8_t b3[3][FL_HID / 32];
+#pragma unroll
+    for (int cc = 0; cc < 3; ++cc)
+#pragma unroll
+      for (int ks = 0; ks < FL_HID / 32; ++ks)
+        b3[cc][ks] = load_bfrag(wl + FB_W3T, FL_HID, 48 * wave + 16 * cc, ks * 32, lane);
+    float bias2[2], bias3[3];
+#pragma unroll
+    for (int cc = 0; cc < 2; ++cc) bias2[cc] = m[FO_B2 + (2 * wave + cc) * 16 + ri];
+#pragma unroll
+    for (int cc = 0; cc < 3; ++cc) {
+      const int col = (3 * wave + cc) * 16 + ri;
+      bias3[cc] = col < FL_NOUT ? m[FO_B3 + col] : 0.f;
+    }
+    const H1Frag u1 = load_h1_frag(m, wave, lane);
+    __syncthreads();  // v of the previous layer
+    if (spl) {
+      const float c = v[se][kFlowC[l][sc]];
+      cond[se][sc] = c;
+      if constexpr (BWD) {
+        vin[l][se][sc] = v[se][kFlowX[l][sc]];
+        s.COND[bwd_at(s, l, sev, 4, sc)] = sev < B ? c : 0.5f;
+      }
+    }
+    __syncthreads();
+    mlp_h1(u1, cond, h1, kEvTile);
+    __syncthreads();
+#pragma unroll
+    for (int cc = 0; cc < 2; ++cc) {
+      f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < FL_HID / 32; ++ks)
+        acc = mfma_step(*reinterpret_cast<const bf16x8_t*>(h1 + ri * FL_LDA + ks * 32 + kq8), b2.f[cc][ks], acc);
+      const int col = (2 * wave + cc) * 16 + ri;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const uint16_t h = f2bf(fmaxf(acc[j] + bias2[cc], 0.f));
+        h2[(kq + j) * FL_LDA + col] = h;
+        if constexpr (BWD) {
+          const int bit = 8 * l + 4 * cc + j;
+          m2 |= static_cast<uint64_t>(bf2f(h) > 0.f) << bit;
+          m1 |= static_cast<uint64_t>(bf2f(h1[(kq + j) * FL_LDA + col]) > 0.f) << bit;
+        }
+      }
+    }
+    __syncthreads();
+    _Float16* const pl = par[BWD ? l : 0];
+#pragma unroll
+    for (int cc = 0; cc < 3; ++cc) {
+      f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < FL_HID / 32; ++ks)
+        acc = mfma_step(*reinterpret_cast<const bf16x8_t*>(h2 + ri * FL_LDA + ks * 32 + kq8), b3[cc][ks], acc);
+      const int col = (3 * wave + cc) * 16 + ri;  // parameter col % 47 of coordinate col / 47
+      if (col < FL_NOUT) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          pl[(kq + j) * FL_LDQ + (col / FL_NPAR) * FL_SPS + col % FL_NPAR] = static_cast<_Float16>(acc[j] + bias3[cc]);
+      }
+    }
+    __syncthreads();
+    if (spl) {
+      float ld = 0.f;
+      const int d = kFlowX[l][sc];
+      v[se][d] = spline_eval<false>(pl + se * FL_LDQ + sc * FL_SPS, v[se][d], ld);
+      // the event's four log s' (lanes 4e .. 4e+3): sums over lane pairs, then pairs of pairs
+      ld += quad_xor<0xB1>(ld);
+      ld += quad_xor<0x4E>(ld);
+      lq += ld;
+    } else if constexpr (BWD) {
+      // meanwhile the activations, 8 events of a feature at a time
+      for (int i = tid - 64; i < 4 * FL_HID; i += 192) {
+        const int j = i >> 2, half = i & 1;
+        const uint16_t* h = (i & 2) ? h2 : h1;
+        uint16_t t[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) t[e] = h[(8 * half + e) * FL_LDA + j];
+        uint4 o;
+        __builtin_memcpy(&o, t, sizeof(o));
+        *reinterpret_cast<uint4*>(((i & 2) ? s.H2 : s.H1) + bwd_at(s, l, e0 + 8 * half, FL_HID, j)) = o;
+      }
+    }
+  }
+  if (spl && sc == 0 && sev < B) logq[sev] = lq;
+  if constexpr (BWD) {
+    const float glq = sev < B ? static_cast<float>(-wev / scal[0]) : 0.f;
+    __syncthreads();
+    for (int l = FL_NLAYER - 1; l >= 0; --l) {
+      const float* m = master + l * FL_LAYER;
+      const uint16_t* wl = wb + static_cast<int64_t>(l) * FB_LAYER;
+      WFrags<FL_NOUTP / 32> n3;
+      load_wfrags(n3, wl + FB_W3N, FL_NOUTP, wave, lane);
+      WFrags<FL_HID / 32> n2;
+      load_wfrags(n2, wl + FB_W2N, FL_HID, wave, lane);
+      if (spl) {
+        // spline reverse sweep: thread (event, transformed coordinate)
+        const _Float16* p = par[l] + se * FL_LDQ + sc * FL_SPS;
+        float raw[FL_NPAR], rb[FL_NPAR];
+#pragma unroll
+        for (int i = 0; i < FL_NPAR; ++i) raw[i] = static_cast<float>(p[i]);
+        if (sev < B) {
+          Knots K;
+          make_knots(raw, K);
+          const int d = kFlowX[l][sc];
+          g[se][d] = rqs_bwd(raw, K, vin[l][se][sc], g[se][d], glq, rb);
+        } else {
+#pragma unroll
+          for (int i = 0; i < FL_NPAR; ++i) rb[i] = 0.f;
+        }
+        float* q = gp + se * FL_LDP + sc * FL_NPAR;
+#pragma unroll
+        for (int i = 0; i < FL_NPAR; ++i) q[i] = rb[i];
+        if (sc == 3) {  // the 4 padded columns (188..191) of the event's row
+#pragma unroll
+          for (int i = 0; i < FL_NOUTP - FL_NOUT; ++i) q[FL_NPAR + i] = 0.f;
+        }
+      } else {
+        for (int i = tid - 64; i < 4 * FL_HID; i += 192) w1[i] = m[FO_W1 + i];
+      }
+      __syncthreads();
+      for (int i = tid; i < 2 * FL_NOUTP; i += 256) {
+        const int c = i >> 1, half = i & 1;
+        float t[8];
+        uint16_t b[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          t[e] = gp[(8 * half + e) * FL_LDP + c];
+          b[e] = f2bf(t[e]);
+          gb[(8 * half + e) * FL_LDP + c] = b[e];
+        }
+        uint4 o;
+        __builtin_memcpy(&o, b, sizeof(o));
+        *reinterpret_cast<uint4*>(s.DRb + bwd_at(s, l, e0 + 8 * half, FL_NOUTP, c)) = o;
+        float4* f = reinterpret_cast<float4*>(s.DRf + bwd_at(s, l, e0 + 8 * half, FL_NOUTP, c));
+        f[0] = make_float4(t[0], t[1], t[2], t[3]);
+        f[1] = make_float4(t[4], t[5], t[6], t[7]);
+      }
+      __syncthreads();
+      // dh2 = dp W3^T (mask h2 > 0)
+      float dh[2][4];
+#pragma unroll
+      for (int cc = 0; cc < 2; ++cc) {
+        f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < FL_NOUTP / 32; ++ks)
+          acc = mfma_step(*reinterpret_cast<const bf16x8_t*>(gb + ri * FL_LDP + ks * 32 + kq8), n3.f[cc][ks], acc);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) dh[cc][j] = (m2 >> (8 * l + 4 * cc + j)) & 1 ? acc[j] : 0.f;
+      }
+      __syncthreads();  // gb is read by every wave above; reuse it for dh2 (bf16) below
+#pragma unroll
+      for (int cc = 0; cc < 2; ++cc) {
+        const int col = (2 * wave + cc) * 16 + ri;
+        uint16_t b[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          b[j] = f2bf(dh[cc][j]);
+          gb[(kq + j) * FL_LDA + col] = b[j];
+        }
+        uint2 o;
+        __builtin_memcpy(&o, b, sizeof(o));
+        *reinterpret_cast<uint2*>(s.DH2b + bwd_at(s, l, e0 + kq, FL_HID, col)) = o;
+        *reinterpret_cast<float4*>(s.DH2f + bwd_at(s, l, e0 + kq, FL_HID, col)) =
+            make_float4(dh[cc][0], dh[cc][1], dh[cc][2], dh[cc][3]);
+      }
+      __syncthreads();
+      // dh1 = dh2 W2^T (mask h1 > 0)
+#pragma unroll
+      for (int cc = 0; cc < 2; ++cc) {
+        f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < FL_HID / 32; ++ks)
+          acc = mfma_step(*reinterpret_cast<const bf16x8_t*>(gb + ri * FL_LDA + ks * 32 + kq8), n2.f[cc][ks], acc);
+        const int col = (2 * wave + cc) * 16 + ri;
+        float t[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          t[j] = (m1 >> (8 * l + 4 * cc + j)) & 1 ? acc[j] : 0.f;
+          gp[(kq + j) * FL_LDP + col] = t[j];
+        }
+        *reinterpret_cast<float4*>(s.DH1f + bwd_at(s, l, e0 + kq, FL_HID, col)) = make_float4(t[0], t[1], t[2], t[3]);
+      }
+      __syncthreads();
+      // dcond = dh1 W1^T; the conditioning coordinates' gradient = gout + dcond
+      if (l > 0 && spl) {
+        float a = 0.f;
+        for (int k = 0; k < FL_HID; ++k) a += gp[se * FL_LDP + k] * w1[sc * FL_HID + k];
+        g[se][kFlowC[l][sc]] += a;
+      }
+      __syncthreads();
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// weight gradients, split over the batch (split-K): split sp of a layer sums the
 // events [sp kc, (sp + 1) kc) into its own partial row; a second kernel adds the
-// rows in split order (deterministic) and writes the layer's slice of grad.
-//   dW3 = H2^T DR, dW2 = H1^T DH2 on MFMA (16 events per step);
+// rows in split order (deterministic).
+//   dW3 = H2^T DR, dW2 = H1^T DH2 on MFMA (32 events per step);
 //   dW1 = COND^T DH1, db1..db3 = column sums, on the VALU
+// A wave takes 2 x 3 (dW3) or 2 x 2 (dW2) output tiles of 16 x 16, so that each operand it
+// loads is used two or three times; each tile's sum is the same chain of steps as alone.
 // ---------------------------------------------------------------------------
 constexpr int kWgTiles = 96 + 64;                  // 16x16 output tiles: dW3 (8 x 12), dW2 (8 x 8)
 constexpr int kWgValu = 512 + 128 + 128 + FL_NOUT;  // dW1, db1, db2, db3
 constexpr int kWgPart = kWgTiles * 256 + kWgValu;   // floats per split
 constexpr int kWgMaxSplit = 64;
-constexpr int kWgBlocksX = (kWgTiles + (kWgValu + 63) / 64 + 3) / 4;
+constexpr int kWgMfmaBlocks = 8;       // 16 waves of dW3, 16 of dW2
+constexpr int kWgD1Blocks = 4, kWgD2Blocks = 2, kWgDrBlocks = 3;  // column sums: 32, 64, 64 features a block
+constexpr int kWgBlocksX = kWgMfmaBlocks + kWgD1Blocks + kWgD2Blocks + kWgDrBlocks;
 
-// C(16x16 at m0, n0) = sum_k A[m][k] B[k][n] with A = Ht (feature-major [m][ld]) and
-// B = Dt ([n][ld]) over k in [k_lo, k_hi) (multiples of 32): lane l supplies
-// Ht[m0 + l%16][k0 + 8(l/16) .. +7] and Dt[n0 + l%16][k0 + 8(l/16) .. +7], one
-// 16-byte load each
-__device__ __forceinline__ f32x4_t mfma_tn(const uint16_t* __restrict__ Ht, const uint16_t* __restrict__ Dt,
-                                           int64_t ld, int m0, int n0, int64_t k_lo, int64_t k_hi, int lane) {
-  f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-  const uint16_t* ap = Ht + (m0 + (lane & 15)) * ld + 8 * (lane >> 4);
-  const uint16_t* bp = Dt + (n0 + (lane & 15)) * ld + 8 * (lane >> 4);
+// C(16x16 tiles at m0 + 16 i, n0 + 16 j) = sum_k A[m][k] B[k][n] over the events [k_lo, k_hi)
+// (multiples of 32), A and B feature-major with MF and NF features: lane l supplies
+// feature m0 + l%16 (n0 + l%16) of events k0 + 8(l/16) .. +7, one 16-byte load each
+template <int MT, int NT>
+__device__ __forceinline__ void wgrad_tiles(const uint16_t* __restrict__ Ht, int MF, const uint16_t* __restrict__ Dt,
+                                            int NF, int m0, int n0, int64_t k_lo, int64_t k_hi, int lane, float* out,
+                                            int tile0, int ldt) {
+  f32x4_t acc[MT][NT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const uint16_t* ap = Ht + (m0 + (lane & 15)) * 32 + 8 * (lane >> 4);
+  const uint16_t* bp = Dt + (n0 + (lane & 15)) * 32 + 8 * (lane >> 4);
 #pragma unroll 4
   for (int64_t k0 = k_lo; k0 < k_hi; k0 += 32) {
-    const bf16x8_t a = *reinterpret_cast<const bf16x8_t*>(ap + k0);
-    const bf16x8_t b = *reinterpret_cast<const bf16x8_t*>(bp + k0);
-    acc = mfma_step(a, b, acc);
+    bf16x8_t a[MT], b[NT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i) a[i] = *reinterpret_cast<const bf16x8_t*>(ap + k0 * MF + 512 * i);
+#pragma unroll
+    for (int j = 0; j < NT; ++j) b[j] = *reinterpret_cast<const bf16x8_t*>(bp + k0 * NF + 512 * j);
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) acc[i][j] = mfma_step(a[i], b[j], acc[i][j]);
   }
-  return acc;
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) out[(tile0 + (m0 / 16 + i) * ldt + n0 / 16 + j) * 256 + lane * 4 + r] = acc[i][j][r];
 }
 
-// sum over k in [k_lo, k_hi) (multiples of 4) of x[k] (y == nullptr) or x[k] y[k]
-__device__ __forceinline__ float dot_run(const float* __restrict__ x, const float* __restrict__ y, int64_t k_lo,
-                                         int64_t k_hi) {
+// column sums of NF features of x over the events [k_lo, k_hi), and with DOT also their
+// products with the four features of c: out[feature], and dout[4][ldd].  Chunks of 256
+// events: every thread forms the sums of 4 consecutive events for some (feature, quad) from
+// 16-byte loads, all in flight together; then one thread per sum adds the chunk's 64 quads
+// in order from LDS.  (One thread per sum reading its own run, a chain of loads, took
+// most of 31 us for 4096 events x 6 layers.)
+constexpr int kQuads = 64;  // per chunk
+template <int NF, bool DOT>
+__device__ __forceinline__ void column_sums(const float* __restrict__ x, int FX, int nf, const float* __restrict__ c,
+                                            int64_t k_lo, int64_t k_hi, float* lds, float* out, float* dout, int ldd) {
+  constexpr int NS = DOT ? 5 : 1;             // sums per feature
+  constexpr int ROUNDS = NF * kQuads / 256;
+  const int tid = threadIdx.x, q = tid & 7, g8 = (tid >> 3) & 7, f0 = tid >> 6;  // quad of a group, group, feature
   float a = 0.f;
-#pragma unroll 4
-  for (int64_t k = k_lo; k < k_hi; k += 4) {
-    const float4 u = *reinterpret_cast<const float4*>(x + k);
-    if (y) {
-      const float4 v = *reinterpret_cast<const float4*>(y + k);
-      a += u.x * v.x + u.y * v.y + u.z * v.z + u.w * v.w;
-    } else {
-      a += u.x + u.y + u.z + u.w;
+  for (int64_t k0 = k_lo; k0 < k_hi; k0 += 4 * kQuads) {
+    const int64_t ev = k0 + 32 * g8 + 4 * q;
+    const bool in = ev < k_hi;
+    float4 u[ROUNDS], v[DOT ? 4 : 1];
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+      const int f = f0 + 4 * r;
+      u[r] = in && f < nf ? *reinterpret_cast<const float4*>(x + (k0 + 32 * g8) * FX + f * 32 + 4 * q)
+                          : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    if constexpr (DOT)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        v[j] = in ? *reinterpret_cast<const float4*>(c + (k0 + 32 * g8) * 4 + j * 32 + 4 * q)
+                  : make_float4(0.f, 0.f, 0.f, 0.f);
+    __syncthreads();  // the chunk before this one has been added
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+      float* o = lds + (f0 + 4 * r) * (kQuads + 1) + 8 * g8 + q;
+      o[0] = u[r].x + u[r].y + u[r].z + u[r].w;
+      if constexpr (DOT)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          o[(1 + j) * NF * (kQuads + 1)] = __fmaf_rn(
+              u[r].w, v[j].w, __fmaf_rn(u[r].z, v[j].z, __fmaf_rn(u[r].x, v[j].x, u[r].y * v[j].y)));
+    }
+    __syncthreads();
+    if (tid < NS * NF) {
+      const float* o = lds + tid * (kQuads + 1);
+      const int nq = static_cast<int>(k_hi - k0 < 4 * kQuads ? (k_hi - k0) / 4 : kQuads);
+#pragma unroll 8
+      for (int k = 0; k < nq; ++k) a += o[k];
     }
   }
-  return a;
-}
-
-// k_hi is the batch rounded up to 32 (the padded rows hold zero gradients)
-__global__ __launch_bounds__(256) void k_flow_wgrad_part(int64_t Bp, int kc, FlowBwdBufs s, float* part) {
-  const int lane = threadIdx.x & 63;
-  const int wave_g = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int64_t k_lo = static_cast<int64_t>(blockIdx.y) * kc;
-  const int64_t k_hi = k_lo + kc < Bp ? k_lo + kc : Bp;
-  float* out = part + static_cast<int64_t>(blockIdx.y) * kWgPart;
-  if (wave_g < 96) {
-    const int mb = wave_g / 12, nb = wave_g % 12;
-    const f32x4_t acc = mfma_tn(s.H2, s.DRb, s.ld, mb * 16, nb * 16, k_lo, k_hi, lane);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) out[wave_g * 256 + lane * 4 + j] = acc[j];
-  } else if (wave_g < kWgTiles) {
-    const int t = wave_g - 96, mb = t / 8, nb = t % 8;
-    const f32x4_t acc = mfma_tn(s.H1, s.DH2b, s.ld, mb * 16, nb * 16, k_lo, k_hi, lane);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) out[wave_g * 256 + lane * 4 + j] = acc[j];
-  } else {
-    const int t = (wave_g - kWgTiles) * 64 + lane;
-    float a = 0.f;
-    if (t < 512) a = dot_run(s.COND + (t / FL_HID) * s.ld, s.DH1f + (t % FL_HID) * s.ld, k_lo, k_hi);
-    else if (t < 640) a = dot_run(s.DH1f + (t - 512) * s.ld, nullptr, k_lo, k_hi);
-    else if (t < 768) a = dot_run(s.DH2f + (t - 640) * s.ld, nullptr, k_lo, k_hi);
-    else if (t < kWgValu) a = dot_run(s.DRf + (t - 768) * s.ld, nullptr, k_lo, k_hi);
-    if (t < kWgValu) out[kWgTiles * 256 + t] = a;
+  const int f = tid % NF, j = tid / NF;
+  if (tid < NS * NF && f < nf) {
+    if (j == 0) out[f] = a;
+    else dout[(j - 1) * ldd + f] = a;
   }
 }
 
-__global__ void k_flow_wgrad_sum(int nsplit, const float* __restrict__ part, float* grad_layer) {
+// k_hi is the batch rounded up to 32 (the padded rows hold zero gradients).  Bound by the
+// latency of its loads (170 MB at 4096 events x 6 layers, mostly from L2): 22 us for six layers, which
+// took 6 x 17 one by one
+__global__ __launch_bounds__(256) void k_flow_wgrad_part(int64_t Bp, int kc, FlowBwdBufs s, float* part) {
+  __shared__ float lds[5 * 32 * (kQuads + 1)];
+  const int lane = threadIdx.x & 63, slot = blockIdx.z;
+  const int64_t k_lo = static_cast<int64_t>(blockIdx.y) * kc;
+  const int64_t k_hi = k_lo + kc < Bp ? k_lo + kc : Bp;
+  float* out = part + (static_cast<int64_t>(slot) * gridDim.y + blockIdx.y) * kWgPart;
+  float* vout = out + kWgTiles * 256;  // dW1 [4][128], db1, db2, db3
+  const int64_t g0 = slot * s.groups * 32;  // the layer's first event position
+  int b = blockIdx.x;  // the column sums, a longer chain, first
+  if (b < kWgD1Blocks) {
+    column_sums<32, true>(s.DH1f + g0 * FL_HID + b * 32 * 32, FL_HID, 32, s.COND + g0 * 4, k_lo, k_hi, lds,
+                          vout + 512 + 32 * b, vout + 32 * b, FL_HID);
+    return;
+  }
+  b -= kWgD1Blocks;
+  if (b < kWgD2Blocks) {
+    column_sums<64, false>(s.DH2f + g0 * FL_HID + b * 64 * 32, FL_HID, 64, nullptr, k_lo, k_hi, lds, vout + 640 + 64 * b,
+                           nullptr, 0);
+    return;
+  }
+  b -= kWgD2Blocks;
+  if (b < kWgDrBlocks) {
+    column_sums<64, false>(s.DRf + g0 * FL_NOUTP + b * 64 * 32, FL_NOUTP, min(64, FL_NOUT - 64 * b), nullptr, k_lo, k_hi,
+                           lds, vout + 768 + 64 * b, nullptr, 0);
+    return;
+  }
+  const int wave_g = (b - kWgDrBlocks) * 4 + (threadIdx.x >> 6);
+  if (wave_g < 16) {
+    wgrad_tiles<2, 3>(s.H2 + g0 * FL_HID, FL_HID, s.DRb + g0 * FL_NOUTP, FL_NOUTP, 32 * (wave_g / 4), 48 * (wave_g % 4),
+                      k_lo, k_hi, lane, out, 0, 12);
+  } else {
+    const int t = wave_g - 16;
+    wgrad_tiles<2, 2>(s.H1 + g0 * FL_HID, FL_HID, s.DH2b + g0 * FL_HID, FL_HID, 32 * (t / 4), 32 * (t % 4), k_lo, k_hi,
+                      lane, out, 96, 8);
+  }
+}
+
+// Adam on the FP32 master weights (bias-corrected, step t >= 1), and the BF16 copies
+struct AdamArgs {
+  float *master, *m1, *m2;  // master == nullptr: the gradient only
+  uint16_t* wb;
+  float lr, b1, b2, eps, c1, c2;
+};
+
+__device__ __forceinline__ void adam_update(const AdamArgs& p, int i, float g) {
+  const float a = p.b1 * p.m1[i] + (1.f - p.b1) * g;
+  const float v = p.b2 * p.m2[i] + (1.f - p.b2) * g * g;
+  p.m1[i] = a;
+  p.m2[i] = v;
+  const float w = p.master[i] - p.lr * (a / p.c1) / (sqrtf(v / p.c2) + p.eps);
+  p.master[i] = w;
+  const int l = i / FL_LAYER, o = i % FL_LAYER;
+  uint16_t* wl = p.wb + static_cast<int64_t>(l) * FB_LAYER;
+  if (o >= FO_W2 && o < FO_B2) {
+    const int q = o - FO_W2, in = q / FL_HID, out = q % FL_HID;
+    const uint16_t b = f2bf(w);
+    wl[FB_W2T + out * FL_HID + in] = b;
+    wl[FB_W2N + q] = b;
+  } else if (o >= FO_W3 && o < FO_B3) {
+    const int q = o - FO_W3, in = q / FL_NOUT, out = q % FL_NOUT;
+    const uint16_t b = f2bf(w);
+    wl[FB_W3T + out * FL_HID + in] = b;
+    wl[FB_W3N + in * FL_NOUTP + out] = b;
+  }
+}
+
+// adds the splits' rows of layer layer0 + blockIdx.y in order; then the gradient goes to
+// `grad`, or straight into Adam
+__global__ __launch_bounds__(256) void k_flow_wgrad_sum(int nsplit, const float* __restrict__ part, int layer0,
+                                                        float* grad, AdamArgs ad) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= kWgPart) return;
+  const float* row = part + static_cast<int64_t>(blockIdx.y) * nsplit * kWgPart + idx;
   float a = 0.f;
-  for (int sp = 0; sp < nsplit; ++sp) a += part[static_cast<int64_t>(sp) * kWgPart + idx];
+  int sp = 0;
+  for (; sp + 8 <= nsplit; sp += 8) {
+    float t[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) t[k] = row[static_cast<int64_t>(sp + k) * kWgPart];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) a += t[k];
+  }
+  for (; sp < nsplit; ++sp) a += row[static_cast<int64_t>(sp) * kWgPart];
+  int o = -1;
   if (idx < kWgTiles * 256) {
     const int tile = idx / 256, r = idx % 256, lane = r / 4, j = r % 4;
     const int row16 = 4 * (lane >> 4) + j, col16 = lane & 15;
     if (tile < 96) {
-      const int row = (tile / 12) * 16 + row16, col = (tile % 12) * 16 + col16;
-      if (col < FL_NOUT) grad_layer[FO_W3 + row * FL_NOUT + col] = a;
+      const int rw = (tile / 12) * 16 + row16, col = (tile % 12) * 16 + col16;
+      if (col < FL_NOUT) o = FO_W3 + rw * FL_NOUT + col;
     } else {
       const int t = tile - 96;
-      grad_layer[FO_W2 + ((t / 8) * 16 + row16) * FL_HID + (t % 8) * 16 + col16] = a;
+      o = FO_W2 + ((t / 8) * 16 + row16) * FL_HID + (t % 8) * 16 + col16;
     }
   } else {
     const int t = idx - kWgTiles * 256;
-    if (t < 512) grad_layer[FO_W1 + t] = a;  // [c][n] with c = t / 128
-    else if (t < 640) grad_layer[FO_B1 + t - 512] = a;
-    else if (t < 768) grad_layer[FO_B2 + t - 640] = a;
-    else grad_layer[FO_B3 + t - 768] = a;
+    if (t < 512) o = FO_W1 + t;  // [c][n] with c = t / 128
+    else if (t < 640) o = FO_B1 + t - 512;
+    else if (t < 768) o = FO_B2 + t - 640;
+    else o = FO_B3 + t - 768;
   }
+  if (o < 0) return;
+  const int i = (layer0 + blockIdx.y) * FL_LAYER + o;
+  if (ad.master) adam_update(ad, i, a);
+  else grad[i] = a;
 }
 
 // ---------------------------------------------------------------------------
 // loss terms: W = sum w (one block, fixed order), glq_i = -w_i / W; loss = -sum w log q / W
+// (formed only for a caller that reads it)
 // ---------------------------------------------------------------------------
-__global__ void k_flow_seed(const double* __restrict__ w, int64_t B, float* glq, double* scal) {
+__global__ __launch_bounds__(256) void k_flow_wsum(const double* __restrict__ w, BatchIdx bx, int64_t B, double* scal) {
   __shared__ double red[256];
   double s = 0.0;
-  for (int64_t i = threadIdx.x; i < B; i += blockDim.x) s += w[i];
+  int64_t i = threadIdx.x;
+  for (; i + 15 * 256 < B; i += 16 * 256) {  // sixteen loads in flight, added in order
+    double t[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) t[k] = w[batch_at(bx, i + 256 * k)];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) s += t[k];
+  }
+  for (; i < B; i += 256) s += w[batch_at(bx, i)];
   red[threadIdx.x] = s;
   __syncthreads();
   for (int st = 128; st > 0; st >>= 1) {
     if (threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
     __syncthreads();
   }
-  const double W = red[0];
-  for (int64_t i = threadIdx.x; i < B; i += blockDim.x) glq[i] = static_cast<float>(-w[i] / W);
-  if (threadIdx.x == 0) scal[0] = W;
+  if (threadIdx.x == 0) scal[0] = red[0];
 }
 
-__global__ void k_flow_loss(const double* __restrict__ w, const float* __restrict__ logq, int64_t B, double* scal) {
+__global__ void k_flow_seed(const double* __restrict__ w, int64_t B, float* glq, const double* scal) {
+  const double W = scal[0];
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < B;
+       i += static_cast<int64_t>(gridDim.x) * blockDim.x)
+    glq[i] = static_cast<float>(-w[i] / W);
+}
+
+__global__ __launch_bounds__(256) void k_flow_loss(const double* __restrict__ w, BatchIdx bx,
+                                                   const float* __restrict__ logq, int64_t B, double* scal) {
   __shared__ double red[256];
   double s = 0.0;
-  for (int64_t i = threadIdx.x; i < B; i += blockDim.x) s += w[i] * static_cast<double>(logq[i]);
+  for (int64_t i = threadIdx.x; i < B; i += blockDim.x) s += w[batch_at(bx, i)] * static_cast<double>(logq[i]);
   red[threadIdx.x] = s;
   __syncthreads();
   for (int st = 128; st > 0; st >>= 1) {
@@ -566,26 +984,12 @@ __global__ void k_flow_loss(const double* __restrict__ w, const float* __restric
   if (threadIdx.x == 0) scal[1] = -red[0] / scal[0];
 }
 
-// Adam on the FP32 master weights (bias-corrected), step t >= 1
-__global__ void k_flow_adam(float* master, const float* grad, float* m1, float* m2, float lr, float b1, float b2,
-                            float eps, float c1, float c2) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < FL_NPARAMS; i += gridDim.x * blockDim.x) {
-    const float g = grad[i];
-    const float a = b1 * m1[i] + (1.f - b1) * g;
-    const float v = b2 * m2[i] + (1.f - b2) * g * g;
-    m1[i] = a;
-    m2[i] = v;
-    master[i] -= lr * (a / c1) / (sqrtf(v / c2) + eps);
-  }
-}
-
-// batch gather through the bijection i -> (a i + c) mod n (a odd and coprime to n)
-__global__ void k_flow_gather(const float* __restrict__ y, const double* __restrict__ w, int64_t n, uint64_t a,
-                              uint64_t c, int64_t start, int64_t B, float* yb, double* wb) {
+// the batch's points and weights in order (layer-by-layer path only)
+__global__ void k_flow_gather(const float* __restrict__ y, const double* __restrict__ w, BatchIdx bx, int64_t B,
+                              float* yb, double* wb) {
   for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < B;
        i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-    const uint64_t j = static_cast<uint64_t>(start + i) % static_cast<uint64_t>(n);
-    const uint64_t idx = (a * j + c) % static_cast<uint64_t>(n);  // a, j, c < n < 2^31: no overflow
+    const int64_t idx = batch_at(bx, i);
     for (int d = 0; d < FL_NDIM; ++d) yb[i * FL_NDIM + d] = y[idx * FL_NDIM + d];
     wb[i] = w[idx];
   }
@@ -636,7 +1040,7 @@ struct vegas_flow_state {
   double *scal; // [4] sum w, loss
   FlowBwdBufs bw;
   float *zs, *lqs;  // sampling buffers [max_sample][8], [max_sample]
-  float* wpart;     // [kWgMaxSplit][kWgPart] split-K partials of the weight gradients
+  float* wpart;     // [layers][splits][kWgPart] split-K partials of the weight gradients
   uint64_t adam_t;
   hipEvent_t ev_ready, ev_used;  // cross-stream ordering with a VEGAS handle's stream
 };
@@ -659,6 +1063,9 @@ int flow_prep(vegas_flow_state* f) {
   VF_HIP(hipGetLastError());
   return VEGAS_OK;
 }
+
+// densities of up to this many events run their six layers in one launch
+constexpr int64_t kFusedDensity = 16384;
 
 // forward-kernel blocks: three resident per CU (LDS 44 KB, at most 168 VGPRs); more tiles
 // per block amortise the per-launch load of the weights into registers
@@ -684,36 +1091,67 @@ int flow_forward(vegas_flow_state* f, const float* y, int64_t B) {
   return VEGAS_OK;
 }
 
-// gradient of L = -sum w log q / sum w over the batch (f->yb, f->wbat) into f->grad
-int flow_backward(vegas_flow_state* f, const double* w, int64_t B, double* loss_host) {
-  hipLaunchKernelGGL(k_flow_seed, dim3(1), dim3(256), 0, f->stream, w, B, f->glq, f->scal);
+// loss and gradient of L = -sum w log q / sum w over the batch bx of (y, w): the gradient
+// into f->grad, or (ad.master) through Adam into the parameters
+int flow_gradient(vegas_flow_state* f, const float* y, const double* w, BatchIdx bx, int64_t B, const AdamArgs& ad,
+                  double* loss_host) {
+  const int64_t Bp = (B + 31) / 32 * 32;  // rows past B (written by the backward) hold zero gradients
+  int kc = kWgSplit;
+  if ((Bp + kc - 1) / kc > kWgMaxSplit) kc = static_cast<int>(((Bp + kWgMaxSplit - 1) / kWgMaxSplit + 31) / 32 * 32);
+  const int nsplit = static_cast<int>((Bp + kc - 1) / kc);
+  FlowBwdBufs bw = f->bw;
+  bw.groups = Bp / 32;
+  auto launch_wgrad = [&](int nl) {
+    hipLaunchKernelGGL(k_flow_wgrad_part, dim3(kWgBlocksX, nsplit, nl), dim3(256), 0, f->stream, Bp, kc, bw, f->wpart);
+  };
+  hipLaunchKernelGGL(k_flow_wsum, dim3(1), dim3(256), 0, f->stream, w, bx, B, f->scal);
   VF_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_flow_loss, dim3(1), dim3(256), 0, f->stream, w, f->logq, B, f->scal);
-  VF_HIP(hipGetLastError());
-  const int64_t stride = static_cast<int64_t>(f->max_batch) * FL_NDIM;
-  float* gout = f->G;           // dL/d z = 0 (uniform base density)
-  float* gin = f->G + stride;
-  hipLaunchKernelGGL(k_flow_zero, dim3(grid_for(B * FL_NDIM, 256, 1024)), dim3(256), 0, f->stream, gout,
-                     B * FL_NDIM);
-  VF_HIP(hipGetLastError());
-  for (int l = FL_NLAYER - 1; l >= 0; --l) {
-    hipLaunchKernelGGL(k_flow_layer_bwd, dim3(grid_for(B, FL_TILE, 4096)), dim3(256), 0, f->stream, f->master, f->wb,
-                       l, f->V + l * stride, gout, gin, f->glq, B, f->bw);
+  if (B <= kFusedBatch) {
+    hipLaunchKernelGGL(k_flow_events<true>, dim3(static_cast<unsigned>(Bp / kEvTile)), dim3(256), 0, f->stream, f->master,
+                       f->wb, y, w, bx, f->scal, f->logq, B, bw);
     VF_HIP(hipGetLastError());
-    const int64_t Bp = (B + 31) / 32 * 32;  // rows past B (written by the backward) hold zero gradients
-    int kc = 256;
-    if ((Bp + kc - 1) / kc > kWgMaxSplit) kc = static_cast<int>(((Bp + kWgMaxSplit - 1) / kWgMaxSplit + 31) / 32 * 32);
-    const int nsplit = static_cast<int>((Bp + kc - 1) / kc);
-    hipLaunchKernelGGL(k_flow_wgrad_part, dim3(kWgBlocksX, nsplit), dim3(256), 0, f->stream, Bp, kc, f->bw, f->wpart);
+    launch_wgrad(FL_NLAYER);
     VF_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_flow_wgrad_sum, dim3((kWgPart + 255) / 256), dim3(256), 0, f->stream, nsplit, f->wpart,
-                       f->grad + l * FL_LAYER);
+    hipLaunchKernelGGL(k_flow_wgrad_sum, dim3((kWgPart + 255) / 256, FL_NLAYER), dim3(256), 0, f->stream, nsplit, f->wpart,
+                       0, f->grad, ad);
     VF_HIP(hipGetLastError());
-    float* t = gout;
-    gout = gin;
-    gin = t;
+  } else {
+    const float* yb = y;
+    const double* wbat = w;
+    if (bx.n) {
+      hipLaunchKernelGGL(k_flow_gather, dim3(grid_for(B, 256, 1024)), dim3(256), 0, f->stream, y, w, bx, B, f->yb, f->wbat);
+      VF_HIP(hipGetLastError());
+      yb = f->yb;
+      wbat = f->wbat;
+    }
+    const int rc = flow_forward(f, yb, B);
+    if (rc != VEGAS_OK) return rc;
+    hipLaunchKernelGGL(k_flow_seed, dim3(grid_for(B, 256, 1024)), dim3(256), 0, f->stream, wbat, B, f->glq, f->scal);
+    VF_HIP(hipGetLastError());
+    const int64_t stride = static_cast<int64_t>(f->max_batch) * FL_NDIM;
+    float* gout = f->G;           // dL/d z = 0 (uniform base density)
+    float* gin = f->G + stride;
+    hipLaunchKernelGGL(k_flow_zero, dim3(grid_for(B * FL_NDIM, 256, 1024)), dim3(256), 0, f->stream, gout, B * FL_NDIM);
+    VF_HIP(hipGetLastError());
+    for (int l = FL_NLAYER - 1; l >= 0; --l) {
+      hipLaunchKernelGGL(k_flow_layer_bwd, dim3(grid_for(B, FL_TILE, 4096)), dim3(256), 0, f->stream, f->master, f->wb,
+                         l, f->V + l * stride, gout, gin, f->glq, B, bw);
+      VF_HIP(hipGetLastError());
+      launch_wgrad(1);
+      VF_HIP(hipGetLastError());
+      // the layers below still need this layer's weights unchanged only in their own
+      // backward, which reads their own weights: Adam may follow each layer's gradient
+      hipLaunchKernelGGL(k_flow_wgrad_sum, dim3((kWgPart + 255) / 256, 1), dim3(256), 0, f->stream, nsplit, f->wpart, l,
+                         f->grad, ad);
+      VF_HIP(hipGetLastError());
+      float* t = gout;
+      gout = gin;
+      gin = t;
+    }
   }
   if (loss_host) {
+    hipLaunchKernelGGL(k_flow_loss, dim3(1), dim3(256), 0, f->stream, w, bx, f->logq, B, f->scal);
+    VF_HIP(hipGetLastError());
     double sc[2];
     VF_HIP(hipMemcpyAsync(sc, f->scal, sizeof(sc), hipMemcpyDeviceToHost, f->stream));
     VF_HIP(hipStreamSynchronize(f->stream));
@@ -747,12 +1185,16 @@ int vegas_flow_create(int32_t max_batch, int64_t max_sample, uint64_t seed, void
   const size_t o_V = take(4 * 7 * Bm * FL_NDIM), o_G = take(4 * 2 * Bm * FL_NDIM);
   const size_t o_logq = take(4 * Bm), o_glq = take(4 * Bm), o_yb = take(4 * Bm * FL_NDIM), o_wbat = take(8 * Bm);
   const size_t o_scal = take(8 * 4);
-  const size_t Bl = (Bm + FL_TILE - 1) / FL_TILE * FL_TILE;  // row stride of the feature-major buffers
+  // the weight gradients' operands: six layers of a batch that runs in one launch, or one
+  // layer of a larger one
+  const size_t Bf = std::min<size_t>(Bm, kFusedBatch);
+  const size_t Bl = std::max((Bf + 31) / 32 * 32 * FL_NLAYER, (Bm + 31) / 32 * 32);
+  const size_t nsp = std::min<size_t>((Bm + 255) / 256, kWgMaxSplit);
   const size_t o_H1 = take(2 * Bl * FL_HID), o_H2 = take(2 * Bl * FL_HID), o_DRb = take(2 * Bl * FL_NOUTP);
   const size_t o_DH2b = take(2 * Bl * FL_HID), o_DRf = take(4 * Bl * FL_NOUTP), o_DH2f = take(4 * Bl * FL_HID);
   const size_t o_DH1f = take(4 * Bl * FL_HID), o_COND = take(4 * Bl * 4);
   const size_t o_zs = take(4 * S * FL_NDIM), o_lqs = take(4 * S);
-  const size_t o_wpart = take(4 * static_cast<size_t>(kWgMaxSplit) * kWgPart);
+  const size_t o_wpart = take(4 * FL_NLAYER * nsp * kWgPart);
   if (hipMalloc(&f->mem, off) != hipSuccess) {
     delete f;
     return VEGAS_ENOMEM;
@@ -778,7 +1220,7 @@ int vegas_flow_create(int32_t max_batch, int64_t max_sample, uint64_t seed, void
   f->bw.DH2f = reinterpret_cast<float*>(b + o_DH2f);
   f->bw.DH1f = reinterpret_cast<float*>(b + o_DH1f);
   f->bw.COND = reinterpret_cast<float*>(b + o_COND);
-  f->bw.ld = static_cast<int64_t>(Bl);
+  f->bw.groups = 0;  // set per batch
   f->zs = reinterpret_cast<float*>(b + o_zs);
   f->lqs = reinterpret_cast<float*>(b + o_lqs);
   f->wpart = reinterpret_cast<float*>(b + o_wpart);
@@ -831,6 +1273,12 @@ int vegas_flow_set_params(vegas_flow f, const float* src_dev) {
 
 int vegas_flow_density(vegas_flow f, const float* y_dev, int64_t B, float* logq_dev) {
   if (!f || !y_dev || !logq_dev || B < 1 || B > f->max_batch) return VEGAS_EINVAL;
+  if (B <= kFusedDensity) {
+    hipLaunchKernelGGL(k_flow_events<false>, dim3(grid_for(B, kEvTile, 1 << 20)), dim3(256), 0, f->stream, f->master, f->wb,
+                       y_dev, nullptr, BatchIdx{}, nullptr, logq_dev, B, f->bw);
+    VF_HIP(hipGetLastError());
+    return VEGAS_OK;
+  }
   const int rc = flow_forward(f, y_dev, B);
   if (rc != VEGAS_OK) return rc;
   VF_HIP(hipMemcpyAsync(logq_dev, f->logq, sizeof(float) * B, hipMemcpyDeviceToDevice, f->stream));
@@ -840,9 +1288,7 @@ int vegas_flow_density(vegas_flow f, const float* y_dev, int64_t B, float* logq_
 int vegas_flow_loss_grad(vegas_flow f, const float* y_dev, const double* w_dev, int64_t B, float* grad_dev,
                          double* loss_host) {
   if (!f || !y_dev || !w_dev || B < 1 || B > f->max_batch) return VEGAS_EINVAL;
-  int rc = flow_forward(f, y_dev, B);
-  if (rc != VEGAS_OK) return rc;
-  rc = flow_backward(f, w_dev, B, loss_host);
+  const int rc = flow_gradient(f, y_dev, w_dev, BatchIdx{}, B, AdamArgs{}, loss_host);
   if (rc != VEGAS_OK) return rc;
   if (grad_dev) VF_HIP(hipMemcpyAsync(grad_dev, f->grad, sizeof(float) * FL_NPARAMS, hipMemcpyDeviceToDevice, f->stream));
   return VEGAS_OK;
@@ -880,21 +1326,14 @@ int vegas_flow_train_step(vegas_flow f, const float* y_dev, const double* w_dev,
     c = static_cast<uint64_t>(s1) % n;
   }
   const int64_t B = batch;
-  hipLaunchKernelGGL(k_flow_gather, dim3(grid_for(B, 256, 1024)), dim3(256), 0, f->stream, y_dev, w_dev, n_data, a, c,
-                     start, B, f->yb, f->wbat);
-  VF_HIP(hipGetLastError());
-  int rc = flow_forward(f, f->yb, B);
-  if (rc != VEGAS_OK) return rc;
-  rc = flow_backward(f, f->wbat, B, loss_host);
-  if (rc != VEGAS_OK) return rc;
   f->adam_t++;
   const float b1 = 0.9f, b2 = 0.999f;
   const float c1 = 1.f - std::pow(b1, static_cast<float>(f->adam_t));
   const float c2 = 1.f - std::pow(b2, static_cast<float>(f->adam_t));
-  hipLaunchKernelGGL(k_flow_adam, dim3(512), dim3(256), 0, f->stream, f->master, f->grad, f->m1, f->m2, lr, b1, b2,
-                     1e-8f, c1, c2);
-  VF_HIP(hipGetLastError());
-  return flow_prep(f);
+  const int rc = flow_gradient(f, y_dev, w_dev, BatchIdx{static_cast<uint64_t>(n_data), a, c, static_cast<uint64_t>(start), ~uint64_t(0) / n_data}, B,
+                               AdamArgs{f->master, f->m1, f->m2, f->wb, lr, b1, b2, 1e-8f, c1, c2}, loss_host);
+  if (rc != VEGAS_OK) f->adam_t--;
+  return rc;
 }
 
 int vegas_flow_sample(vegas_flow f, const float* z_dev, int64_t n, float* y_dev, float* logq_dev) {
