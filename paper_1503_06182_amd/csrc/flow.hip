@@ -362,21 +362,13 @@ __global__ __launch_bounds__(256) void k_flow_layer_bwd(const float* __restrict_
       const int e = tid >> 2, j = tid & 3;
       const int64_t ev = e0 + e;
       float* p = &par[e * FL_LDP + j * FL_NPAR];
-      float raw[FL_NPAR], rb[FL_NPAR];
-#pragma unroll
-      for (int i = 0; i < FL_NPAR; ++i) raw[i] = p[i];
       if (ev < B) {
-        Knots K;
-        make_knots(raw, K);
         const int d = kFlowX[l][j];
-        const float xb = rqs_bwd(raw, K, vin[ev * FL_NDIM + d], gout[ev * FL_NDIM + d], glq[ev], rb);
-        gin[ev * FL_NDIM + d] = xb;
+        gin[ev * FL_NDIM + d] = rqs_bwd(p, vin[ev * FL_NDIM + d], gout[ev * FL_NDIM + d], glq[ev], p);
       } else {
 #pragma unroll
-        for (int i = 0; i < FL_NPAR; ++i) rb[i] = 0.f;
+        for (int i = 0; i < FL_NPAR; ++i) p[i] = 0.f;
       }
-#pragma unroll
-      for (int i = 0; i < FL_NPAR; ++i) p[i] = rb[i];  // each thread owns its 47 entries
       if (j == 3) {  // the 4 padded columns (188..191) of the event's row
 #pragma unroll
         for (int i = 0; i < FL_NOUTP - FL_NOUT; ++i) p[FL_NPAR + i] = 0.f;
@@ -625,21 +617,14 @@ __global__ __launch_bounds__(256) void k_flow_events(const float* __restrict__ m
       if (spl) {
         // spline reverse sweep: thread (event, transformed coordinate)
         const _Float16* p = par[l] + se * FL_LDQ + sc * FL_SPS;
-        float raw[FL_NPAR], rb[FL_NPAR];
-#pragma unroll
-        for (int i = 0; i < FL_NPAR; ++i) raw[i] = static_cast<float>(p[i]);
+        float* q = gp + se * FL_LDP + sc * FL_NPAR;
         if (sev < B) {
-          Knots K;
-          make_knots(raw, K);
           const int d = kFlowX[l][sc];
-          g[se][d] = rqs_bwd(raw, K, vin[l][se][sc], g[se][d], glq, rb);
+          g[se][d] = rqs_bwd(p, vin[l][se][sc], g[se][d], glq, q);
         } else {
 #pragma unroll
-          for (int i = 0; i < FL_NPAR; ++i) rb[i] = 0.f;
+          for (int i = 0; i < FL_NPAR; ++i) q[i] = 0.f;
         }
-        float* q = gp + se * FL_LDP + sc * FL_NPAR;
-#pragma unroll
-        for (int i = 0; i < FL_NPAR; ++i) q[i] = rb[i];
         if (sc == 3) {  // the 4 padded columns (188..191) of the event's row
 #pragma unroll
           for (int i = 0; i < FL_NOUTP - FL_NOUT; ++i) q[FL_NPAR + i] = 0.f;
@@ -974,7 +959,19 @@ __global__ __launch_bounds__(256) void k_flow_loss(const double* __restrict__ w,
                                                    const float* __restrict__ logq, int64_t B, double* scal) {
   __shared__ double red[256];
   double s = 0.0;
-  for (int64_t i = threadIdx.x; i < B; i += blockDim.x) s += w[batch_at(bx, i)] * static_cast<double>(logq[i]);
+  int64_t i = threadIdx.x;
+  for (; i + 15 * 256 < B; i += 16 * 256) {
+    double t[16];
+    float q[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      t[k] = w[batch_at(bx, i + 256 * k)];
+      q[k] = logq[i + 256 * k];
+    }
+#pragma unroll
+    for (int k = 0; k < 16; ++k) s += t[k] * static_cast<double>(q[k]);
+  }
+  for (; i < B; i += 256) s += w[batch_at(bx, i)] * static_cast<double>(logq[i]);
   red[threadIdx.x] = s;
   __syncthreads();
   for (int st = 128; st > 0; st >>= 1) {
