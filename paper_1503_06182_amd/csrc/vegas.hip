@@ -3,7 +3,7 @@
 // Sec. 2.1-2.2).
 //
 // One iteration is three or four launches on the handle's stream:
-//   k_event     one event per lane (grid-stride): Philox point -> grid map ->
+//   k_event     one event per lane, 64 at a time (a CU's waves draw them): Philox point -> grid map ->
 //               phase space -> PDFs x |M|^2 -> weight; writes the event record
 //               (w, packed bin indices) and the exact max |w|.  From the second
 //               iteration on it also adds each event's exact digits of w, w^2
@@ -270,7 +270,7 @@ __device__ __forceinline__ void acc_sums_to_lds(LaneSums& ls, long long* acc) {
 // digits, 5 x 1e7 W+W- events 1515 -> 1491 us, 3 x 3e6 hadronic 588 -> 576 (there also a
 // third wave per SIMD, which the smaller LDS allows), 5 x 9e5 stratified W+ 363 -> 351.
 // ---------------------------------------------------------------------------
-constexpr int kFoldEvents = 32768;           // events of a block between two carries
+constexpr uint32_t kFoldEvents = 32768;      // events of a block between two carries
 constexpr int kLds2 = 3;                     // LDS digits of a grid slot's w^2
 constexpr int kLdsObs = 6;                   // LDS digits of an observable bin
 constexpr unsigned long long kMask48 = 0xffffffffffffull, kMask32 = 0xffffffffull;
@@ -392,7 +392,6 @@ struct EventArgs {
 // ---------------------------------------------------------------------------
 // K1: events
 // ---------------------------------------------------------------------------
-// waves per SIMD the register allocation must allow with 256-thread blocks
 constexpr double kExtLo = 0x1p-40, kExtHi = 1.0 - 0x1p-40;
 
 // (W+W- with four spills 20 bytes a lane and ran the same 1500 us per 5 x 1e7 events; the
@@ -400,6 +399,28 @@ constexpr double kExtLo = 0x1p-40, kExtHi = 1.0 - 0x1p-40;
 template <int PROC>
 constexpr int event_min_waves() {
   return PROC == VEGAS_WW_HAD || PROC == VEGAS_WW_4L ? 3 : 4;
+}
+// threads of a block that fills a CU at that budget
+template <int PROC>
+constexpr int event_threads() {
+  return 4 * kWave * event_min_waves<PROC>();
+}
+
+// the kernel's arguments, read again by scalar loads where they are used: hoisted out of the
+// event loop, the integrand's constants took more scalar registers than there are and
+// were read back lane by lane on the VALU (W+W-: 36 of 872 instructions of a pass; the
+// hadronic kernel's spills to memory fall from 60 to 28 bytes a lane)
+__device__ __forceinline__ const EventArgs& reload_args() {
+  auto p = (const __attribute__((address_space(4))) EventArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  VG_OPAQUE_SGPR(p);
+  return *(const EventArgs*)p;
+}
+
+// 0 that the compiler takes for a different value in each lane
+__device__ __forceinline__ int lane_zero() {
+  int z = 0;
+  asm volatile("" : "+v"(z));
+  return z;
 }
 
 // EXT: the point is the learned proposal's y (binary32, kept inside the open unit
@@ -414,7 +435,7 @@ constexpr int event_min_waves() {
 // digits of the hypercube (dimension 0 the least significant).
 template <int PROC, int PREC, int D, int MAXT, bool EXT = false, bool FUSED = false, bool OBS = false,
           bool STRAT = false>
-__global__ __launch_bounds__(MAXT, (MAXT == 256 ? event_min_waves<PROC>() : 1)) void k_event(EventArgs a) {
+__global__ __launch_bounds__(MAXT) void k_event(EventArgs a) {
   extern __shared__ unsigned char smem[];
   const int n = a.nbins, nd = D > 0 ? D : a.ndim;
   const int nslot = nd * n, ncol_h = hist_cols(nslot);
@@ -428,17 +449,20 @@ __global__ __launch_bounds__(MAXT, (MAXT == 256 ? event_min_waves<PROC>() : 1)) 
   // with 10 or more dimensions the register budget of 2 waves per SIMD is spent on the
   // integrand, so the lane's S1, S2 digit sums live in LDS, one private slot per lane
   // and digit (no atomics: no other lane touches it) instead of 10 registers
-  constexpr bool kLdsSums = FUSED && D >= 10 && MAXT == 256;
-  long long* lsum = acc + fcol;  // kLdsSums: [kFoldLane][256]
+  constexpr bool kLdsSums = FUSED && D >= 10 && MAXT == event_threads<PROC>();
+  long long* lsum = acc + fcol;  // kLdsSums: [kFoldLane][blockDim.x]
+  const int lsn = static_cast<int>(blockDim.x);
   if constexpr (kLdsSums)
 #pragma unroll
-    for (int k = 0; k < kFoldLane; ++k) lsum[k * 256 + threadIdx.x] = 0;
+    for (int k = 0; k < kFoldLane; ++k) lsum[k * lsn + threadIdx.x] = 0;
   if (blockIdx.x == 0) {
     // clear this iteration's digit totals (the previous iteration's were consumed
     // by its finalisation, earlier on the stream)
     for (int i = threadIdx.x; i < ncol; i += blockDim.x) a.b.acc_tot[i] = 0;
-
   }
+  __shared__ uint32_t draw;  // the block's next chunk of 64 events that no wave has taken
+  const uint32_t nwave = blockDim.x / kWave;
+  if (threadIdx.x == 0) draw = nwave;
   int E1 = 0, E2 = 0;
   if constexpr (FUSED) {
     E1 = a.b.fxs[1];
@@ -447,135 +471,146 @@ __global__ __launch_bounds__(MAXT, (MAXT == 256 ? event_min_waves<PROC>() : 1)) 
   __syncthreads();
 
   long long ls[kFoldLane] = {0, 0, 0, 0, 0};
-  // per-lane counts fit 32 bits (fewer than 2^31 events per launch), and so does the
-  // event index: both keep registers free for the integrand
+  // event indices fit 32 bits (fewer than 2^31 events per launch), which keeps registers
+  // free for the integrand; the counts are the wave's, in scalar registers
   unsigned long long wmax = 0ull;
   uint32_t nz = 0u, nnf = 0u;
-  const int32_t step = static_cast<int32_t>(gridDim.x * blockDim.x);
   const int32_t nev32 = static_cast<int32_t>(a.nev);
-  int32_t i = static_cast<int32_t>(blockIdx.x * blockDim.x + threadIdx.x);
-  // FUSED: at most kFoldEvents events of the block between two carries; `rest` is the
-  // distance to the end from the block's first event of the stretch (block-uniform)
-  const int32_t stretch = kFoldEvents / static_cast<int32_t>(blockDim.x);
-  int32_t rest = nev32 - static_cast<int32_t>(blockIdx.x * blockDim.x);
+  // the block's chunks are blockIdx, blockIdx + gridDim, ...: its waves draw them from the
+  // LDS counter, so all of them end within one chunk of each other.  (Equal numbers of
+  // chunks per wave do not: a SIMD serves its oldest wave first, and at 4e6 W+ events the
+  // blocks of 4 waves ended between 42 and 73 us, the last ones alone on their SIMDs.)
+  const uint32_t nchunk = (static_cast<uint32_t>(nev32) + kWave - 1) / kWave;
+  const uint32_t mine = blockIdx.x < nchunk ? (nchunk - blockIdx.x + gridDim.x - 1) / gridDim.x : 0u;
+  uint32_t* const drawp = &draw + lane_zero();
+  // FUSED: at most kFoldEvents events of the block between two carries
+  uint32_t lim = FUSED ? min(mine, kFoldEvents / kWave) : mine;
+  uint32_t first = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   for (;;) {
-    for (int32_t pass = stretch; (!FUSED || pass > 0) && i < nev32; --pass, i += step) {
-      double u[D > 0 ? D : VEGAS_MAX_DIM], x[D > 0 ? D : VEGAS_MAX_DIM];
-      // wave priorities: the uniforms (integer work) at the base priority, the grid map
-      // (the grid's LDS loads) one step up, the integrand at the top, so that a SIMD
-      // issues the floating-point work of waves already past their loads first and the
-      // waves of a block drift apart in phase (W+W- 340 against 366 us per 1e7-event
-      // launch, hadronic W+W- 490 against 532, with the fold there back at the base
-      // priority; the light W+ kernel is unchanged)
-      __builtin_amdgcn_s_setprio(0);
-      int bins[D > 0 ? D : VEGAS_MAX_DIM];
-      if constexpr (EXT) {
-#pragma unroll
-        for (int d = 0; d < (D > 0 ? D : VEGAS_MAX_DIM); ++d) {
-          if (d >= nd) break;
-          const double v = static_cast<double>(a.ext_y[static_cast<int64_t>(i) * nd + d]);
-          u[d] = fmin(fmax(v, kExtLo), kExtHi);
-        }
-      } else {
-        event_uniforms<D>(a.seed, a.iter, static_cast<uint64_t>(i), nd, u);
-        if constexpr (STRAT) {
-          uint32_t hc = a.s_cube ? static_cast<uint32_t>(a.s_cube[i]) : udiv(static_cast<uint32_t>(i), a.div_npc);
-          const uint32_t m = static_cast<uint32_t>(a.strata_m);
-#pragma unroll
+    for (uint32_t c = first; c < lim;) {
+      uint32_t nx = 0;
+      if ((threadIdx.x & (kWave - 1)) == 0) nx = atomicAdd(drawp, 1u);  // taken up below, after the events
+      const int32_t i = static_cast<int32_t>((c * gridDim.x + blockIdx.x) * kWave + (threadIdx.x & (kWave - 1)));
+      double w = 0.0;
+      bool bad = false;
+      if (i < nev32) {
+        double u[D > 0 ? D : VEGAS_MAX_DIM], x[D > 0 ? D : VEGAS_MAX_DIM];
+        // wave priorities: the uniforms (integer work) at the base priority, the grid map
+        // (the grid's LDS loads) one step up, the integrand at the top, so that a SIMD
+        // issues the floating-point work of waves already past their loads first and the
+        // waves of a block drift apart in phase (W+W- 340 against 366 us per 1e7-event
+        // launch, hadronic W+W- 490 against 532, with the fold there back at the base
+        // priority; the light W+ kernel is unchanged)
+        __builtin_amdgcn_s_setprio(0);
+        int bins[D > 0 ? D : VEGAS_MAX_DIM];
+        if constexpr (EXT) {
+  #pragma unroll
           for (int d = 0; d < (D > 0 ? D : VEGAS_MAX_DIM); ++d) {
             if (d >= nd) break;
-            const uint32_t q = udiv(hc, a.div_m);
-            u[d] = (static_cast<double>(hc - q * m) + u[d]) / a.strata_md;
-            hc = q;
+            const double v = static_cast<double>(a.ext_y[static_cast<int64_t>(i) * nd + d]);
+            u[d] = fmin(fmax(v, kExtLo), kExtHi);
+          }
+        } else {
+          event_uniforms<D>(a.seed, a.iter, static_cast<uint64_t>(i), nd, u);
+          if constexpr (STRAT) {
+            uint32_t hc = a.s_cube ? static_cast<uint32_t>(a.s_cube[i]) : udiv(static_cast<uint32_t>(i), a.div_npc);
+            const uint32_t m = static_cast<uint32_t>(a.strata_m);
+  #pragma unroll
+            for (int d = 0; d < (D > 0 ? D : VEGAS_MAX_DIM); ++d) {
+              if (d >= nd) break;
+              const uint32_t q = udiv(hc, a.div_m);
+              u[d] = (static_cast<double>(hc - q * m) + u[d]) / a.strata_md;
+              hc = q;
+            }
+          }
+        }
+        __builtin_amdgcn_s_setprio(1);
+        const double J = grid_map<D>(e_lds, n, nd, u, x, bins);
+        __builtin_amdgcn_s_setprio(3);
+        // the bins, 4 of 8 bits per word.  With 10 or more fixed dimensions they are
+        // recorded before the integrand, so that only the packed words stay live across
+        // it (the fused fold takes the bins back out of them); with fewer, or a run-time
+        // dimension, keeping the bins themselves allocates better
+        constexpr int kWords = D > 0 ? (D + 3) / 4 : 4;
+        constexpr bool kEarlyBins = D >= 10;
+        uint32_t bw[kWords];
+        if constexpr (kEarlyBins) {
+  #pragma unroll
+          for (int g = 0; g < kWords; ++g) {
+            bw[g] = 0u;
+  #pragma unroll
+            for (int j = 0; j < 4; ++j)
+              if (4 * g + j < nd) bw[g] |= static_cast<uint32_t>(bins[4 * g + j]) << (8 * j);
+            a.b.rec_bins[g * a.stride_rec + i] = bw[g];
+          }
+        }
+        double q;
+        const double f = integrand<PROC, PREC, D>(reload_args().pc, x, q);
+        w = J * f;
+        if constexpr (STRAT && !EXT)
+          if (a.s_cube) w *= a.s_N / (a.s_Hd * static_cast<double>(a.s_cnt[a.s_cube[i]]));
+        int obin = 0;
+        if constexpr (OBS) {
+          obin = obs_bin(obs_is_square<PROC>() ? sqrt(q) : q, a.obs_lo, a.obs_hi, a.obs_scale, a.nobs);
+          a.b.rec_obs[i] = static_cast<uint8_t>(obin);
+        }
+        if constexpr (EXT) w *= exp(-static_cast<double>(a.ext_lq[i]));
+        bad = !isfinite(w * w);
+        if (bad) w = 0.0;
+        a.b.rec_w[i] = w;
+        if constexpr (!kEarlyBins) {
+  #pragma unroll
+          for (int g = 0; g < kWords; ++g) {
+            if (4 * g >= nd) break;
+            uint32_t word = 0;
+  #pragma unroll
+            for (int j = 0; j < 4; ++j)
+              if (4 * g + j < nd) word |= static_cast<uint32_t>(bins[4 * g + j]) << (8 * j);
+            a.b.rec_bins[g * a.stride_rec + i] = word;
+          }
+        }
+        if constexpr (PROC == VEGAS_WW_HAD) __builtin_amdgcn_s_setprio(0);
+        const unsigned long long wb = static_cast<unsigned long long>(__double_as_longlong(fabs(w)));
+        wmax = wb > wmax ? wb : wmax;
+        if constexpr (FUSED) {
+          if (w != 0.0) {
+            const FoldDigits g = fold_digits<PROC != VEGAS_GENZ>(w, E1, E2);
+            const long long t[kFoldLane] = {g.d[0], g.d[1], g.h[0], g.h[1], g.h[2]};
+  #pragma unroll
+            for (int k = 0; k < kFoldLane; ++k) {
+              if (k == kFoldLane - 1 && !g.top) continue;
+              if constexpr (kLdsSums) lsum[k * lsn + threadIdx.x] += t[k];
+              else ls[k] += t[k];
+            }
+  #pragma unroll
+            for (int d = 0; d < (D > 0 ? D : VEGAS_MAX_DIM); ++d) {
+              if (d >= nd) break;
+              const int bin = kEarlyBins ? static_cast<int>((bw[d >> 2] >> (8 * (d & 3))) & 0xffu) : bins[d];
+              fold_hist(acc, hist_col(d * n + bin), nslot, g);
+            }
+            if constexpr (OBS) fold_obs(acc, fcol_h + kLdsObs * obin, g);
           }
         }
       }
-      __builtin_amdgcn_s_setprio(1);
-      const double J = grid_map<D>(e_lds, n, nd, u, x, bins);
-      __builtin_amdgcn_s_setprio(3);
-      // the bins, 4 of 8 bits per word.  With 10 or more fixed dimensions they are
-      // recorded before the integrand, so that only the packed words stay live across
-      // it (the fused fold takes the bins back out of them); with fewer, or a run-time
-      // dimension, keeping the bins themselves allocates better
-      constexpr int kWords = D > 0 ? (D + 3) / 4 : 4;
-      constexpr bool kEarlyBins = D >= 10;
-      uint32_t bw[kWords];
-      if constexpr (kEarlyBins) {
-#pragma unroll
-        for (int g = 0; g < kWords; ++g) {
-          bw[g] = 0u;
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            if (4 * g + j < nd) bw[g] |= static_cast<uint32_t>(bins[4 * g + j]) << (8 * j);
-          a.b.rec_bins[g * a.stride_rec + i] = bw[g];
-        }
-      }
-      double q;
-      const double f = integrand<PROC, PREC, D>(a.pc, x, q);
-      double w = J * f;
-      if constexpr (STRAT && !EXT)
-        if (a.s_cube) w *= a.s_N / (a.s_Hd * static_cast<double>(a.s_cnt[a.s_cube[i]]));
-      int obin = 0;
-      if constexpr (OBS) {
-        obin = obs_bin(obs_is_square<PROC>() ? sqrt(q) : q, a.obs_lo, a.obs_hi, a.obs_scale, a.nobs);
-        a.b.rec_obs[i] = static_cast<uint8_t>(obin);
-      }
-      if constexpr (EXT) w *= exp(-static_cast<double>(a.ext_lq[i]));
-      if (!isfinite(w * w)) {
-        ++nnf;
-        w = 0.0;
-      } else if (w != 0.0) {
-        ++nz;
-      }
-      a.b.rec_w[i] = w;
-      if constexpr (!kEarlyBins) {
-#pragma unroll
-        for (int g = 0; g < kWords; ++g) {
-          if (4 * g >= nd) break;
-          uint32_t word = 0;
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            if (4 * g + j < nd) word |= static_cast<uint32_t>(bins[4 * g + j]) << (8 * j);
-          a.b.rec_bins[g * a.stride_rec + i] = word;
-        }
-      }
-      if constexpr (PROC == VEGAS_WW_HAD) __builtin_amdgcn_s_setprio(0);
-      const unsigned long long wb = static_cast<unsigned long long>(__double_as_longlong(fabs(w)));
-      wmax = wb > wmax ? wb : wmax;
-      if constexpr (FUSED) {
-        if (w != 0.0) {
-          const FoldDigits g = fold_digits<PROC != VEGAS_GENZ>(w, E1, E2);
-          const long long t[kFoldLane] = {g.d[0], g.d[1], g.h[0], g.h[1], g.h[2]};
-#pragma unroll
-          for (int k = 0; k < kFoldLane; ++k) {
-            if (k == kFoldLane - 1 && !g.top) continue;
-            if constexpr (kLdsSums) lsum[k * 256 + threadIdx.x] += t[k];
-            else ls[k] += t[k];
-          }
-#pragma unroll
-          for (int d = 0; d < (D > 0 ? D : VEGAS_MAX_DIM); ++d) {
-            if (d >= nd) break;
-            const int bin = kEarlyBins ? static_cast<int>((bw[d >> 2] >> (8 * (d & 3))) & 0xffu) : bins[d];
-            fold_hist(acc, hist_col(d * n + bin), nslot, g);
-          }
-          if constexpr (OBS) fold_obs(acc, fcol_h + kLdsObs * obin, g);
-        }
-      }
+      nz += static_cast<uint32_t>(__popcll(__ballot(w != 0.0)));
+      nnf += static_cast<uint32_t>(__popcll(__ballot(bad)));
+      c = __builtin_amdgcn_readfirstlane(nx);
     }
-    if constexpr (!FUSED) break;
-    if (rest <= static_cast<int64_t>(stretch) * step) break;
-    rest -= stretch * step;
+    if (lim == mine) break;
     if constexpr (FUSED) {
       if constexpr (kLdsSums)
 #pragma unroll
         for (int k = 0; k < kFoldLane; ++k) {
-          ls[k] = lsum[k * 256 + threadIdx.x];
-          lsum[k * 256 + threadIdx.x] = 0;
+          ls[k] = lsum[k * lsn + threadIdx.x];
+          lsum[k * lsn + threadIdx.x] = 0;
         }
+      first = __builtin_amdgcn_readfirstlane(lim + threadIdx.x / kWave);
       fold_sums_to_lds(ls, acc);
 #pragma unroll
       for (int k = 0; k < kFoldLane; ++k) ls[k] = 0;
-      __syncthreads();
+      __syncthreads();  // the histogram is whole, and no wave draws
+      if (threadIdx.x == 0) draw = lim + nwave;
+      lim = min(mine, lim + kFoldEvents / kWave);
       for (int q = threadIdx.x; q < nslot; q += blockDim.x) fold_carry(acc + hist_col(q), nslot);
       if constexpr (OBS)
         for (int q = threadIdx.x; q < 2 * (a.nobs + 2); q += blockDim.x) fold_carry(acc + fcol_h + 3 * q, 1);
@@ -587,16 +622,14 @@ __global__ __launch_bounds__(MAXT, (MAXT == 256 ? event_min_waves<PROC>() : 1)) 
   if (threadIdx.x < 3) blk[threadIdx.x] = 0ull;
   __syncthreads();
   wmax = wave_max_u64(wmax);
-  const long long snz = wave_sum_i64(static_cast<long long>(nz));
-  const long long snf = wave_sum_i64(static_cast<long long>(nnf));
   if ((threadIdx.x & (kWave - 1)) == 0) {
     atomicMax(&blk[0], wmax);
-    atomicAdd(&blk[1], static_cast<unsigned long long>(snz));
-    atomicAdd(&blk[2], static_cast<unsigned long long>(snf));
+    atomicAdd(&blk[1], static_cast<unsigned long long>(nz));
+    atomicAdd(&blk[2], static_cast<unsigned long long>(nnf));
   }
   if constexpr (kLdsSums)
 #pragma unroll
-    for (int k = 0; k < kFoldLane; ++k) ls[k] = lsum[k * 256 + threadIdx.x];
+    for (int k = 0; k < kFoldLane; ++k) ls[k] = lsum[k * lsn + threadIdx.x];
   if constexpr (FUSED) fold_sums_to_lds(ls, acc);
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -1878,7 +1911,8 @@ struct vegas_state {
   size_t smem_max;              // LDS per block the launches may use
   int refine_lds;               // LDS of the refinement scratch: D * 4 (n + 1) doubles
   bool scale_valid;             // the device holds scales from a previous iteration (b.fxs)
-  int ncu, occ_event, occ_event_fused, occ_acc;  // CUs, and resident 256-thread blocks per CU
+  int ncu, occ_event, occ_event_fused;  // CUs, and resident blocks of a full CU's threads (event_full) per CU
+  int occ_acc;                          // resident 256-thread blocks of k_accum per CU
   // optional per-stage kernel timing with HIP events on the handle's stream:
   // bit s set = the kernels of stage s are timed
   uint32_t timing;
@@ -1914,16 +1948,15 @@ namespace {
 
 int pick_threads(const vegas_state* h) { return kWave * (h->wpb > 0 ? h->wpb : 4); }
 
-// grid-stride launches: enough blocks to fill every CU at the kernel's occupancy
-// (one resident wave of blocks), capped by the partial-buffer rows and the knob.  Past
-// one block per CU, whole rounds of blocks (a multiple of the CU count) and at least
-// kMinPasses grid-stride passes per lane: each block also clears and writes a row of
-// digit sums, which few passes do not repay (W+ at 3e5 events: 15.6 us with 256 blocks,
-// 21.0 us with 1024; Drell-Yan at 1e5: 9.2 us with 256, 10.7 us with 391)
+// grid-stride launches: enough blocks to fill every CU at the kernel's occupancy (occ
+// blocks of `unit` threads a CU, one resident wave of blocks), capped by the partial-buffer
+// rows and the knob.  Past one block per CU, whole rounds of blocks (a multiple of the CU
+// count) and at least kMinPasses passes per lane: each block also clears and writes a row
+// of digit sums, which few passes do not repay
 constexpr int64_t kMinPasses = 4;
-int pick_blocks(const vegas_state* h, int64_t nev, int threads, int occ, int rows_cap) {
+int pick_blocks(const vegas_state* h, int64_t nev, int threads, int occ, int unit, int rows_cap) {
   int64_t nb = (nev + threads - 1) / threads;
-  int64_t fill = static_cast<int64_t>(h->ncu) * (occ > 0 ? occ : 1) * 256 / threads;
+  int64_t fill = static_cast<int64_t>(h->ncu) * (occ > 0 ? occ : 1) * unit / threads;
   if (fill < 1) fill = 1;
   const int64_t ncu = h->ncu > 0 ? h->ncu : 1;
   if (h->max_blocks <= 0 && nb > ncu && fill >= ncu) {
@@ -1938,8 +1971,19 @@ int pick_blocks(const vegas_state* h, int64_t nev, int threads, int occ, int row
   return static_cast<int>(nb);
 }
 
-// two instantiations per integrand: up to 4 waves per block (the register budget of a
-// 256-thread block, the performance path) and up to 16 waves (for the launch knob)
+// threads of an event block: 4 waves while that is one block per CU at most, then as many
+// more waves as the CU's share of the events has chunks of 64, up to a full CU (`full`
+// threads).  One block per CU and not several of 4 waves: it clears and writes one row
+// of digits instead of three or four, and its waves share out the chunks (W+ kernel at
+// 4e5 events 21.6 -> 16.5 us, 1e6 31 -> 26, 4e6 75 -> 68; hadronic W+W- 41 -> 30, 58 -> 52,
+// 165 -> 157; W+W- 28 -> 23, 43 -> 41, at 1e7 no different, its VALUs being full).
+int event_block_threads(const vegas_state* h, int64_t nev, int full) {
+  if (h->wpb > 0) return kWave * h->wpb;
+  const int64_t ncu = h->ncu > 0 ? h->ncu : 1;
+  const int64_t w = ((nev + kWave - 1) / kWave + ncu - 1) / ncu;
+  return static_cast<int>(std::min<int64_t>(std::max<int64_t>(w, 4) * kWave, full));
+}
+
 hipEvent_t pool_event(vegas_state* h) {
   if (!h->ev_pool.empty()) {
     hipEvent_t e = h->ev_pool.back();
@@ -1994,16 +2038,26 @@ void stage_collect(vegas_state* h) {
   h->ev_pending.clear();
 }
 
+// LDS of an event block: with 10 or more dimensions the lanes' sums as well
+int event_block_lds(const vegas_state* h, bool fused, int threads) {
+  if (!fused) return h->event_lds;
+  return h->fused_lds + (h->D >= 10 ? static_cast<int>(sizeof(long long)) * kFoldLane * threads : 0);
+}
+
+// two instantiations where a full CU's block (event_threads, the performance path) has
+// fewer than 16 waves: that one, and one of 16 waves for the launch knob
 template <int PROC, int PREC, int D, bool EXT, bool FUSED, bool OBS, bool STRAT>
 hipError_t launch_event_tfo(vegas_state* h, const EventArgs& a, int blocks, int threads) {
+  constexpr int kFull = event_threads<PROC>();
   TimedLaunch t(h, 0);
-  const int lds = FUSED ? h->fused_lds : h->event_lds;
-  if (EXT || threads <= 256)
-    hipExtLaunchKernelGGL((k_event<PROC, PREC, D, 256, EXT, FUSED, OBS, STRAT>), dim3(blocks),
-                          dim3(EXT ? 256 : threads), lds, h->stream, t.e0, t.e1, 0, a);
+  if (threads <= kFull)
+    hipExtLaunchKernelGGL((k_event<PROC, PREC, D, kFull, EXT, FUSED, OBS, STRAT>), dim3(blocks), dim3(threads),
+                          event_block_lds(h, FUSED, threads), h->stream, t.e0, t.e1, 0, a);
+  else if constexpr (!EXT && kFull < 1024)
+    hipExtLaunchKernelGGL((k_event<PROC, PREC, D, 1024, false, FUSED, OBS, STRAT>), dim3(blocks), dim3(threads),
+                          FUSED ? h->fused_lds : h->event_lds, h->stream, t.e0, t.e1, 0, a);
   else
-    hipExtLaunchKernelGGL((k_event<PROC, PREC, D, 1024, false, FUSED, OBS, STRAT>), dim3(blocks), dim3(threads), lds,
-                          h->stream, t.e0, t.e1, 0, a);
+    return hipErrorInvalidConfiguration;
   return t.done();
 }
 
@@ -2044,15 +2098,15 @@ hipError_t launch_event(vegas_state* h, const EventArgs& a, int blocks, int thre
   return hipErrorInvalidValue;
 }
 
-// learned-proposal variants (8-dimensional integrands only, 256-thread blocks)
-hipError_t launch_event_ext(vegas_state* h, const EventArgs& a, int blocks, bool fused) {
+// learned-proposal variants (8-dimensional integrands only)
+hipError_t launch_event_ext(vegas_state* h, const EventArgs& a, int blocks, int threads, bool fused) {
   switch (h->cfg.process) {
-    case VEGAS_GAUSS: return launch_event_t<VEGAS_GAUSS, VEGAS_FP64, 0, true>(h, a, blocks, 256, fused);
-    case VEGAS_GENZ: return launch_event_t<VEGAS_GENZ, VEGAS_FP64, 0, true>(h, a, blocks, 256, fused);
+    case VEGAS_GAUSS: return launch_event_t<VEGAS_GAUSS, VEGAS_FP64, 0, true>(h, a, blocks, threads, fused);
+    case VEGAS_GENZ: return launch_event_t<VEGAS_GENZ, VEGAS_FP64, 0, true>(h, a, blocks, threads, fused);
     case VEGAS_WW_4L:
       if (h->cfg.precision == VEGAS_FP32_ME)
-        return launch_event_t<VEGAS_WW_4L, VEGAS_FP32_ME, 8, true>(h, a, blocks, 256, fused);
-      return launch_event_t<VEGAS_WW_4L, VEGAS_FP64, 8, true>(h, a, blocks, 256, fused);
+        return launch_event_t<VEGAS_WW_4L, VEGAS_FP32_ME, 8, true>(h, a, blocks, threads, fused);
+      return launch_event_t<VEGAS_WW_4L, VEGAS_FP64, 8, true>(h, a, blocks, threads, fused);
     default: return hipErrorInvalidValue;
   }
 }
@@ -2062,10 +2116,17 @@ bool ext_supported(const vegas_state* h) {
   return h->D == 8 && (p == VEGAS_GAUSS || p == VEGAS_GENZ || p == VEGAS_WW_4L);
 }
 
+// threads of a full CU's event block
+int event_full(const vegas_state* h) {
+  static_assert(event_threads<VEGAS_WW_4L>() == event_threads<VEGAS_WW_HAD>());
+  const int p = h->cfg.process;
+  return p == VEGAS_WW_4L || p == VEGAS_WW_HAD ? event_threads<VEGAS_WW_4L>() : event_threads<VEGAS_W_PLUS>();
+}
+
 template <int PROC, int PREC, int D, bool FUSED, bool OBS>
 const void* event_kernel_ptr(bool strat) {
-  return strat ? reinterpret_cast<const void*>(&k_event<PROC, PREC, D, 256, false, FUSED, OBS, true>)
-               : reinterpret_cast<const void*>(&k_event<PROC, PREC, D, 256, false, FUSED, OBS, false>);
+  return strat ? reinterpret_cast<const void*>(&k_event<PROC, PREC, D, event_threads<PROC>(), false, FUSED, OBS, true>)
+               : reinterpret_cast<const void*>(&k_event<PROC, PREC, D, event_threads<PROC>(), false, FUSED, OBS, false>);
 }
 
 template <int PROC, int PREC, int D>
@@ -2075,13 +2136,13 @@ int occupancy_event_t(int lds, bool fused, bool obs, bool strat) {
                                : event_kernel_ptr<PROC, PREC, D, true, false>(strat))
                         : (obs ? event_kernel_ptr<PROC, PREC, D, false, true>(strat)
                                : event_kernel_ptr<PROC, PREC, D, false, false>(strat));
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k, 256, lds) != hipSuccess)
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k, event_threads<PROC>(), lds) != hipSuccess)
     return 1;
   return nb > 0 ? nb : 1;
 }
 
 int occupancy_event(const vegas_state* h, bool fused) {
-  const int lds = fused ? h->fused_lds : h->event_lds;
+  const int lds = event_block_lds(h, fused, event_full(h));
   const bool o = h->nobs > 0, st = h->strata_m > 0;
   switch (h->cfg.process) {
     case VEGAS_GAUSS: return occupancy_event_t<VEGAS_GAUSS, VEGAS_FP64, 0>(lds, fused, o, st);
@@ -2115,11 +2176,10 @@ void configure_lds(vegas_state* h) {
   h->acc_lds = static_cast<int>(sizeof(long long) * (hist_cols(dpg * n) + ocol));
   const int full = static_cast<int>(sizeof(long long) * (hist_cols(D * n) + ocol));
   // the fused fold is used where the finalisation can also re-fold in one block's LDS (the
-  // row's digits beside the grid); its own blocks need less: 48-bit digits and, with 10 or
-  // more dimensions, the lanes' sums ([5][256])
+  // row's digits beside the grid); its own blocks hold 48-bit digits and, with 10 or more
+  // dimensions, the lanes' sums (event_block_lds)
   h->fused_ok = h->event_lds + full + (D >= 10 ? static_cast<int>(sizeof(long long) * kLane * 256) : 0) <= kFusedLdsMax;
-  h->fused_lds = h->event_lds + static_cast<int>(sizeof(long long) * (fold_cols(D * n) + fold_obs_cols(h->nobs) +
-                                                                      (D >= 10 ? kFoldLane * 256 : 0)));
+  h->fused_lds = h->event_lds + static_cast<int>(sizeof(long long) * (fold_cols(D * n) + fold_obs_cols(h->nobs)));
   h->fin_lds = h->fused_ok ? full : 0;
   h->refine_lds = static_cast<int>(sizeof(double) * 4 * D * (n + 1));
   const int obs_lds = h->nobs ? static_cast<int>(sizeof(double) * 2 * (h->nobs + 2)) : 0;
@@ -2390,7 +2450,9 @@ int run_iteration(vegas_handle h, int64_t n_req, const float* ext_y, const float
                        h->s_off, h->s_cube, H);
     VG_HIP(hipGetLastError());
   }
-  const int threads = ext_y ? 256 : pick_threads(h);
+  const int full = event_full(h);
+  int threads = event_block_threads(h, n_events, full);
+  if (ext_y && threads > full) threads = full;
   const int nslot = h->D * h->n;
   EventArgs ea;
   ea.pc = h->pc;
@@ -2420,10 +2482,10 @@ int run_iteration(vegas_handle h, int64_t n_req, const float* ext_y, const float
   // whenever such scales exist and the digits fit in LDS; the choice depends on
   // the history and the configuration only, never on the launch shape
   const bool fused = h->fused_ok && h->scale_valid;
-  const int ev_blocks = fused ? pick_blocks(h, n_events, threads, h->occ_event_fused, kMaxRowsAcc)
-                              : pick_blocks(h, n_events, threads, h->occ_event, kMaxRowsEvent);
+  const int ev_blocks = fused ? pick_blocks(h, n_events, threads, h->occ_event_fused, full, kMaxRowsAcc)
+                              : pick_blocks(h, n_events, threads, h->occ_event, full, kMaxRowsEvent);
   if (ext_y)
-    VG_HIP(launch_event_ext(h, ea, ev_blocks, fused));
+    VG_HIP(launch_event_ext(h, ea, ev_blocks, threads, fused));
   else
     VG_HIP(launch_event(h, ea, ev_blocks, threads, fused));
   int rows = ev_blocks;
@@ -2436,9 +2498,10 @@ int run_iteration(vegas_handle h, int64_t n_req, const float* ext_y, const float
     aa.nbins = h->n;
     aa.dims_per_group = h->acc_dpg;
     aa.nobs = h->nobs;
-    rows = pick_blocks(h, n_events, threads, h->occ_acc, kMaxRowsAcc);
+    const int acc_threads = pick_threads(h);
+    rows = pick_blocks(h, n_events, acc_threads, h->occ_acc, 256, kMaxRowsAcc);
     TimedLaunch t(h, 1);
-    hipExtLaunchKernelGGL(k_accum, dim3(rows, h->acc_groups), dim3(threads), h->acc_lds, h->stream, t.e0, t.e1, 0,
+    hipExtLaunchKernelGGL(k_accum, dim3(rows, h->acc_groups), dim3(acc_threads), h->acc_lds, h->stream, t.e0, t.e1, 0,
                           aa);
     VG_HIP(t.done());
   }
