@@ -52,13 +52,13 @@ sys.path.insert(0, ROOT)
 #    x 2 + WRITE_SIZE x 1 KiB, the factors read from a plain 1 GiB device copy).
 # The counter summaries are under profiles/.
 EVENT_KERNEL_WORK = {
-    ("w_plus", "fp64"): {"algorithmic_f64": 365.1, "f64": 325.2, "f32": 0.0, "traffic": 22_169_771,
+    ("w_plus", "fp64"): {"algorithmic_f64": 341.5, "f64": 325.2, "f32": 0.0, "traffic": 22_169_771,
                          "events": 1_000_000},
     ("ww_4l", "fp64"): {"algorithmic_f64": 813.0, "f64": 1033.7, "f32": 0.0, "traffic": 180_107_630,
                         "events": 10_000_000},
     ("ww_4l", "fp32me"): {"algorithmic_f64": None, "f64": 636.7, "f32": 418.0, "traffic": None,
                           "events": 10_000_000},
-    ("ww_had", "fp64"): {"algorithmic_f64": 1112.0, "f64": 1319.1, "f32": 0.0, "traffic": 216_902_407,
+    ("ww_had", "fp64"): {"algorithmic_f64": 1110.0, "f64": 1319.1, "f32": 0.0, "traffic": 216_902_407,
                          "events": 10_000_000},
 }
 # FP64 FLOPs of one call of the library's version of each mathematical function the

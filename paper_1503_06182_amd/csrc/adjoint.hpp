@@ -200,23 +200,24 @@ __global__ __launch_bounds__(256, 4) void k_dy_grad(GradArgs a) {
             J *= dn * h;
           }
         }
-        double jbw;
-        const double s = bw_map(a.pc, xx[0], a.pc.rho_rng, jbw);
+        const double s = bw_mass(a.pc, xx[0], a.pc.rho_rng), dm = s - a.pc.M2;
+        const double jbw = a.pc.rho_rng * __fma_rn(dm, dm, a.pc.MG2) * a.pc.invMG;
         double L, l1, l2;
         {
 #pragma clang fp contract(off)
-          L = log(s * a.pc.invS);
+          L = log_pos(s * a.pc.invS);
           l1 = xx[1] * L;
           l2 = L - l1;
         }
         const double jtau = -L * a.pc.invS;
         const double cs = 2.0 * xx[2] - 1.0;
         // conv J_grid J_bw J_tau 2 / (2 s) / (16 pi) times e^4 / 12 s^2 2 (1 + cos^2) / s^2
-        K = kc * J * jbw * jtau * (2.0 / s) * (1.0 / (16.0 * kPi)) * (1.0 + cs * cs);
+        K = kc * J * jbw * jtau * (2.0 * rcp_nr(s)) * (1.0 / (16.0 * kPi)) * (1.0 + cs * cs);
         if (K != 0.0) {
           m2 = s;
           ls = L;
-          Ls = fmax(log(expm1(l1) * expm1(l2)), -1e4);
+          const double P = expm1_fin(l1) * expm1_fin(l2);
+          Ls = P > 0.0 ? log_pos(P) : -1e4;
         }
       }
       ev[lane * 4 + 0] = K;

@@ -27,20 +27,23 @@ struct PhysConst {
   // expressions), so that no per-thread copy of them takes vector registers: MG^2,
   // MG (1 + tlo^2), (MZ GZ)^2
   double MG2, MGt, mzgz2;
+  // the constant factors of an event's weight, in one: conversion, flux, phase space,
+  // couplings and the Breit-Wigner maps' ranges
+  double wk = 1.0;
   double invS;                // 1 / S (hadronic)
   double pdfA, pdfa, pdfb;
   int pdf_pow;                // 1: a = a2/2 with integer a2 in [-8, 8] and integer b in [0, 16]
   int pdf_a2, pdf_b;
-  // Drell-Yan: Q_q Q_l and chiral Z couplings g[q][h] * g_l[h'] products
-  double qql[2];              // Q_q * Q_l for q = u, d
-  double gg[2][4];            // g_q,h g_l,h' for (h,h') = LL, LR, RL, RR
+  // Drell-Yan
   double e4_12;               // e^4 / 12
+  double dyA, dyB, dyC;       // sums over q, h, h' of (Q_q Q_l)^2, 2 Q_q Q_l g_q,h g_l,h', (g_q,h g_l,h')^2
   double mzgz, mz2;
   // W+
   double g4v2_24;             // g^4 |V|^2 / 24
   double ptmin2, th2;         // pT^2 cut, tanh(eta_max)^2
   // WW
   double rs, shat, gs;        // sqrt(shat), shat, g / sqrt(2)
+  double i2rs = 1.0;          // 1 / (2 sqrt(shat))
   double cs_re[2][2], cs_im[2][2];  // s-channel photon+Z coefficient, [q][h]
   double ct;                  // exchange-diagram coefficient: -g^2 / 2
   double csR2;                // |Cs[u][R]|^2 + |Cs[d][R]|^2
@@ -106,21 +109,23 @@ __device__ __forceinline__ double atan_rr(double v) {
 // few units in the last place (checked on the CPU against tanl).
 // ---------------------------------------------------------------------------
 // sin y and cos y for |y| <= pi/4 by the minimax polynomials of the fdlibm / FreeBSD msun
-// kernels (k_sin.c, k_cos.c; Sun Microsystems): sin y = y + y^3 (S1 + z R(z)), z = y^2,
-// and cos y = 1 - z/2 + z^2 C(z), the leading 1 - z/2 carried with its rounding error.
-// About one unit in the last place (checked on the CPU against sinl and cosl).
+// kernels (k_sin.c, k_cos.c; Sun Microsystems), by Horner's rule: sin y = y + y z S(z),
+// z = y^2, and cos y = 1 + z (z C(z) - 1/2).  About one unit in the last place (checked on
+// the CPU against sinl and cosl).
 __device__ __forceinline__ void sincos_pio4(double y, double& sn, double& cs) {
-  const double z = y * y, w = z * z;
-  const double rs = __fma_rn(z, __fma_rn(z, poly_coef(2.75573137070700676789e-06), poly_coef(-1.98412698298579493134e-04)),
-                             poly_coef(8.33333333332248946124e-03)) +
-                    z * w * __fma_rn(z, poly_coef(1.58969099521155010221e-10), poly_coef(-2.50507602534068634195e-08));
-  sn = __fma_rn(z * y, __fma_rn(z, rs, poly_coef(-1.66666666666666324348e-01)), y);
-  const double rc = z * __fma_rn(z, __fma_rn(z, poly_coef(2.48015872894767294178e-05), poly_coef(-1.38888888888741095749e-03)),
-                                 poly_coef(4.16666666666666019037e-02)) +
-                    w * w * __fma_rn(z, __fma_rn(z, poly_coef(-1.13596475577881948265e-11), poly_coef(2.08757232129817482790e-09)),
-                                     poly_coef(-2.75573143513906633035e-07));
-  const double hz = 0.5 * z, v = 1.0 - hz;
-  cs = v + (((1.0 - v) - hz) + z * rc);
+  const double z = y * y;
+  double s = __fma_rn(z, poly_coef(1.58969099521155010221e-10), poly_coef(-2.50507602534068634195e-08));
+  s = __fma_rn(z, s, poly_coef(2.75573137070700676789e-06));
+  s = __fma_rn(z, s, poly_coef(-1.98412698298579493134e-04));
+  s = __fma_rn(z, s, poly_coef(8.33333333332248946124e-03));
+  s = __fma_rn(z, s, poly_coef(-1.66666666666666324348e-01));
+  sn = __fma_rn(z * y, s, y);
+  double c = __fma_rn(z, poly_coef(-1.13596475577881948265e-11), poly_coef(2.08757232129817482790e-09));
+  c = __fma_rn(z, c, poly_coef(-2.75573143513906633035e-07));
+  c = __fma_rn(z, c, poly_coef(2.48015872894767294178e-05));
+  c = __fma_rn(z, c, poly_coef(-1.38888888888741095749e-03));
+  c = __fma_rn(z, c, poly_coef(4.16666666666666019037e-02));
+  cs = __fma_rn(z, __fma_rn(z, c, -0.5), 1.0);
 }
 
 // tan y = nm / q on |y| <= pi/4 (the rational fit above)
@@ -156,10 +161,79 @@ __device__ __forceinline__ double tan_halfpi(double x) {
 }
 
 // ---------------------------------------------------------------------------
+// log, exp and expm1 for the parton fractions, without the libraries' extended precision
+// and special cases: about one unit in the last place (checked on the CPU against logl and
+// expm1l).  31, 16 and 20 vector instructions where the library's take 98, 42 and 53; the
+// W+ and Drell-Yan integrands call log once and expm1 twice, the hadronic W+W- one exp once
+// and expm1 twice.  Polynomials: interpolations at Chebyshev nodes, computed in 60 digits.
+// ---------------------------------------------------------------------------
+constexpr double kLn2 = 0.6931471805599453, kLn2Lo = 2.3190468138462996e-17;
+
+// log x for normal x > 0: x = 2^k m with m in [sqrt(1/2), sqrt(2)), f = m - 1,
+// s = f / (m + 1), z = s^2: log m = 2 atanh(s) = f - s (f - z G(z)) with
+// G = 2 (1/3 + z/5 + ...) by a degree-6 polynomial (9.4e-18 of s)
+__device__ __forceinline__ double log_pos(double x) {
+  VG_PRICED(log, x);
+  constexpr uint32_t kSqrtHalf = 0x3fe6a09e;  // high word of sqrt(1/2)
+  uint64_t b;
+  __builtin_memcpy(&b, &x, sizeof(b));
+  const uint32_t h = static_cast<uint32_t>(b >> 32) + (0x3ff00000u - kSqrtHalf);
+  const int k = static_cast<int>(h >> 20) - 1023;
+  const double m = __hiloint2double(static_cast<int>((h & 0xfffffu) + kSqrtHalf), static_cast<int>(b));
+  const double f = m - 1.0, s = f * rcp_nr(m + 1.0), z = s * s;
+  double g = __fma_rn(z, poly_coef(0.146171283998073), poly_coef(0.15331666676597175));
+  g = __fma_rn(z, g, poly_coef(0.1818289077802613));
+  g = __fma_rn(z, g, poly_coef(0.22222211112104948));
+  g = __fma_rn(z, g, poly_coef(0.2857142862611452));
+  g = __fma_rn(z, g, poly_coef(0.399999999998992));
+  g = __fma_rn(z, g, poly_coef(0.666666666666667));
+  const double dk = static_cast<double>(k);
+  const double u = __fma_rn(s, __fma_rn(-z, g, f), dk * -kLn2Lo);
+  return __fma_rn(dk, kLn2, f - u);
+}
+
+// t = k ln 2 + r with |r| <= ln(2)/2; exp(r) - 1 = r + r^2 q(r), q of degree 9 (1.6e-17 of exp r)
+__device__ __forceinline__ double exp_fold(double t, int& k, double& r) {
+  constexpr double kRound = 0x1.8p52;  // a sum with it is rounded to an integer, its last bits
+  const double kr = __fma_rn(t, 1.4426950408889634, kRound);
+  uint64_t b;
+  __builtin_memcpy(&b, &kr, sizeof(b));
+  k = static_cast<int>(static_cast<uint32_t>(b));
+  const double dk = kr - kRound;
+  r = __fma_rn(-dk, kLn2Lo, __fma_rn(-dk, kLn2, t));
+  double q = __fma_rn(r, poly_coef(2.510038549551032e-08), poly_coef(2.7620088445409746e-07));
+  q = __fma_rn(q, r, poly_coef(2.7557268459997064e-06));
+  q = __fma_rn(q, r, poly_coef(2.4801521295954376e-05));
+  q = __fma_rn(q, r, poly_coef(0.00019841269863053618));
+  q = __fma_rn(q, r, poly_coef(0.0013888888917213717));
+  q = __fma_rn(q, r, poly_coef(0.008333333333330062));
+  q = __fma_rn(q, r, poly_coef(0.04166666666662413));
+  q = __fma_rn(q, r, poly_coef(0.16666666666666669));
+  return __fma_rn(q, r, poly_coef(0.5000000000000001));
+}
+
+// exp t and exp t - 1 for |t| < 1e9 (0 and inf, or -1 and inf, where they leave the range)
+__device__ __forceinline__ double exp_fin(double t) {
+  VG_PRICED(exp, t);
+  int k;
+  double r;
+  const double q = exp_fold(t, k, r);
+  return ldexp(__fma_rn(r * r, q, r) + 1.0, k);
+}
+__device__ __forceinline__ double expm1_fin(double t) {
+  VG_PRICED(expm1, t);
+  int k;
+  double r;
+  const double q = exp_fold(t, k, r), s = ldexp(double(1.0), k);
+  return __fma_rn(s * r * r, q, __fma_rn(s, r, s - 1.0));  // 2^k - 1 + 2^k (r + r^2 q)
+}
+
+// ---------------------------------------------------------------------------
 // mappings (rounding kept as in their plain definitions: no contraction)
 // ---------------------------------------------------------------------------
 // m^2 = M^2 + M G tan(rho_lo + r rrng) on the process's window (lower edge m2lo,
-// rho_lo = atan(tlo)); jac = dm^2/dr = rrng ((m^2 - M^2)^2 + (M G)^2) / (M G)
+// rho_lo = atan(tlo)); its Jacobian is dm^2/dr = rrng ((m^2 - M^2)^2 + (M G)^2) / (M G), whose
+// resonance factor the integrands cancel against the propagator's
 template <bool TWO_DIV = false>
 __device__ __forceinline__ double bw_mass(const PhysConst& c, double r, double rrng) {
 #pragma clang fp contract(off)
@@ -185,14 +259,6 @@ __device__ __forceinline__ double bw_mass(const PhysConst& c, double r, double r
   return below ? __fma_rn(c.MGt, t, c.m2lo) : __fma_rn(c.MG, t, c.M2);
 }
 
-__device__ __forceinline__ double bw_map(const PhysConst& c, double r, double rrng, double& jac) {
-#pragma clang fp contract(off)
-  const double m2 = bw_mass(c, r, rrng);
-  const double dm = m2 - c.M2;
-  jac = rrng * (dm * dm + c.MG2) * c.invMG;
-  return m2;
-}
-
 // ---------------------------------------------------------------------------
 // product of the two parton densities, f(x1) f(x2) = A^2 tau^a ((1-x1)(1-x2))^b with
 // tau = x1 x2, L = ln tau and P = (1-x1)(1-x2) (> 0).  For half-integer a and integer
@@ -210,8 +276,12 @@ __device__ __forceinline__ double pdf_pair(const PhysConst& c, double tau, doubl
     const int a2 = c.pdf_a2;
     const int ka = (a2 >= 0 ? a2 : -a2) >> 1;   // |a| rounded down
     double ta = ipow_pos(tau, ka);
-    if (a2 & 1) ta *= sqrt_nr(tau);
-    if (a2 < 0) ta = rcp_nr(ta);
+    if (a2 < 0 && ka > 0) ta = rcp_nr(ta);
+    if (a2 & 1) {
+      double r, ir;
+      sqrt_rsqrt_nr(tau, r, ir);
+      ta *= a2 < 0 ? ir : r;
+    }
     return c.pdfA * c.pdfA * ta * ipow_pos(P, c.pdf_b);
   }
   return c.pdfA * c.pdfA * exp(c.pdfa * L + c.pdfb * log(P));
@@ -281,39 +351,28 @@ __device__ __forceinline__ double f_eemumu(const PhysConst& c, const double* x) 
 // q qbar -> photon/Z -> l- l+ (both beam orderings).  With one PDF for all
 // four flavours the two orderings sum to sum_{hh'} |A_hh'|^2 * 2 (1 + c^2).
 // ---------------------------------------------------------------------------
+// The map's Jacobian contains 1 / |shat - MZ^2 + i MZ GZ|^2's inverse, so with
+// |Q Q'/shat + g g'/D|^2 summed over q, h, h' the weight needs no division by |D|^2:
+// shat^2 |D|^2 sum = A |D|^2 + shat (B (shat - MZ^2) + C shat).
 // obs_sq: the square of the observable, the lepton-pair mass m_ll^2
 __device__ __forceinline__ double f_dy(const PhysConst& c, const double* x, double& obs_sq) {
-  double jbw;
-  const double m2 = bw_map(c, x[0], c.rho_rng, jbw);
+  const double m2 = bw_mass(c, x[0], c.rho_rng);
   obs_sq = m2;
+  const double tau = m2 * c.invS;
   double L, l1, l2;
   {
 #pragma clang fp contract(off)
-    L = log(m2 * c.invS);
+    L = log_pos(tau);
     l1 = x[1] * L;
     l2 = L - l1;
   }
-  const double jtau = -L * c.invS;
   // f(x1) f(x2) with tau = x1 x2 = m2 / S and 1 - x = -expm1(ln x)
-  const double ff = pdf_pair(c, m2 * c.invS, L, expm1(l1) * expm1(l2));
+  const double ff = pdf_pair(c, tau, L, expm1_fin(l1) * expm1_fin(l2));
   const double cs = 2.0 * x[2] - 1.0;
-  // 1 / (shat - MZ^2 + i MZ GZ)
   const double ds = m2 - c.mz2;
-  const double den = rcp_nr(ds * ds + c.mzgz2);
-  const double pre = ds * den, pim = -c.mzgz * den;
-  const double inv_s = rcp_nr(m2);
-  double sum = 0.0;
-#pragma unroll
-  for (int q = 0; q < 2; ++q)
-#pragma unroll
-    for (int hh = 0; hh < 4; ++hh) {
-      const double re = c.qql[q] * inv_s + c.gg[q][hh] * pre;
-      const double im = c.gg[q][hh] * pim;
-      sum += re * re + im * im;
-    }
-  const double me = c.e4_12 * m2 * m2 * sum * 2.0 * (1.0 + cs * cs);
+  const double me = __fma_rn(c.dyA, __fma_rn(ds, ds, c.mzgz2), m2 * __fma_rn(c.dyB, ds, c.dyC * m2));
   // conv * J_bw * J_tau * J_cos(2) * flux 1/(2 shat) * 2 pi / (32 pi^2)
-  return c.conv * jbw * jtau * 2.0 * (0.5 * inv_s) * (1.0 / (16.0 * kPi)) * ff * me;
+  return (c.wk * me) * (-L * rcp_nr(m2)) * __fma_rn(cs, cs, 1.0) * ff;
 }
 
 // ---------------------------------------------------------------------------
@@ -324,32 +383,29 @@ __device__ __forceinline__ double f_dy(const PhysConst& c, const double* x, doub
 // ---------------------------------------------------------------------------
 // obs_sq: the square of the observable, the e+ transverse momentum (taken before the cuts)
 __device__ __forceinline__ double f_w(const PhysConst& c, const double* x, double& obs_sq) {
-  double jbw;
-  const double m2 = bw_map(c, x[0], c.rho_rng, jbw);
+  const double m2 = bw_mass(c, x[0], c.rho_rng);
+  const double tau = m2 * c.invS;
   double L, l1, l2;
   {
 #pragma clang fp contract(off)
-    L = log(m2 * c.invS);
+    L = log_pos(tau);
     l1 = x[1] * L;
     l2 = L - l1;
   }
-  const double jtau = -L * c.invS;
   const double cs = 2.0 * x[2] - 1.0;
   // x = 1 + expm1(ln x): beta = (x1 - x2)/(x1 + x2) and 1 - x from the same two values
-  const double em1 = expm1(l1), em2 = expm1(l2);
+  const double em1 = expm1_fin(l1), em2 = expm1_fin(l2);
   const double pt2 = 0.25 * m2 * (1.0 - cs) * (1.0 + cs);
   obs_sq = pt2;
   const double beta = div_nr(em1 - em2, 2.0 + em1 + em2);
   const double num = cs + beta, dnm = 1.0 + beta * cs;
   const bool pass = (pt2 > c.ptmin2) && (num * num < c.th2 * dnm * dnm);
   if (!pass) return 0.0;
-  const double ds = m2 - c.M2;
-  const double den = ds * ds + c.MG2;
-  // |M|^2 / (2 shat) = g^4 |V|^2 / 24 * shat^2 (1 + cos^2) / den / (2 shat): one division
-  const double me_flux = c.g4v2_24 * (0.5 * m2) * (1.0 + cs * cs) * rcp_nr(den);
-  const double ff = pdf_pair(c, m2 * c.invS, L, em1 * em2);
+  // |M|^2 / (2 shat) = g^4 |V|^2 / 24 * shat^2 (1 + cos^2) / |D|^2 / (2 shat), and the map's
+  // Jacobian has the same |D|^2 = (shat - MW^2)^2 + (MW GW)^2 above the line
+  const double ff = pdf_pair(c, tau, L, em1 * em2);
   // conv * J_bw * J_tau * |M|^2 / (2 shat) * (2 * 2 pi)/(32 pi^2)
-  return c.conv * jbw * jtau * (1.0 / (8.0 * kPi)) * ff * me_flux;
+  return (c.wk * tau) * -L * __fma_rn(cs, cs, 1.0) * ff;
 }
 
 // ---------------------------------------------------------------------------
@@ -546,9 +602,11 @@ __device__ __forceinline__ R ww_me2(const PhysConst& c, const cx<R> ep[4], const
 // amplitude as the one factor 1 / (2 (E + m) x) per W, squared.
 //
 // Bound by the VALU's issue rate; against currents, boosted momenta, four spinor square
-// roots and the vertex the event loop takes about 870 instead of 1156 VALU instructions
+// roots and the vertex the event loop took about 870 instead of 1156 VALU instructions
 // per 64 events and 137 instead of 157 registers: an iteration of 1e7 W+W- events 303 us
-// instead of 378, of 3e6 hadronic ones 196 instead of 221.
+// instead of 378, of 3e6 hadronic ones 196 instead of 221.  (Since then the shorter
+// divisions, roots and sines, and the weight's constant factors formed on the host, have
+// taken it to 838 instructions, and the two iterations to 276 and 172 us.)
 // ---------------------------------------------------------------------------
 // light-cone components of the bosons (the W+ along qx, qz): W+ E -+ qz, W- E -+ qz (its
 // momentum is -qx, -qz), each sum of positive terms or the quotient (m^2 + qx^2) over its
@@ -609,19 +667,34 @@ __device__ __forceinline__ void boost_pair(const R Q[4], R m, R im, const R k[4]
   }
 }
 
-// sin and cos of 2 pi x for 0 <= x <= 1: x = q/4 + r with q = rint(4 x) and |r| <= 1/8
-// (r exact: x and q/4 are within a factor 2 of each other when q > 0), y = 2 pi r, then
-// the rotation by q quarter turns
+// v with its sign changed where bit 31 of m is set
+__device__ __forceinline__ double flip_sign(double v, uint32_t m) {
+  uint64_t b;
+  __builtin_memcpy(&b, &v, sizeof(b));
+  b ^= static_cast<uint64_t>(m & 0x80000000u) << 32;
+  __builtin_memcpy(&v, &b, sizeof(b));
+  return v;
+}
+
+// sin and cos of 2 pi x for -1 <= x <= 1: x = q/4 + r with q = rint(4 x) and |r| <= 1/8
+// (r exact: x and q/4 are within a factor 2 of each other when q is not 0), y = 2 pi r, then
+// the rotation by q quarter turns.  q is rounded by adding 1.5 x 2^52, whose sum's last bits
+// are q's: bit 0 exchanges sine and cosine, bit 1 of q and of q + 1 are their signs
 __device__ __forceinline__ void sincos_2pi(double x, double& s, double& c) {
   VG_PRICED(sincos, x);
-  const double q = rint(4.0 * x);
-  const double y = (x - 0.25 * q) * 6.283185307179586477;
+  constexpr double kRound = 0x1.8p52;
+  const double t = __fma_rn(4.0, x, kRound);
+  const double q = t - kRound;
+  uint64_t bits;
+  __builtin_memcpy(&bits, &t, sizeof(bits));
+  const uint32_t qi = static_cast<uint32_t>(bits);
+  const double y = __fma_rn(-0.25, q, x) * 6.283185307179586477;
   double sn, cs;
   sincos_pio4(y, sn, cs);
-  const int qi = static_cast<int>(q) & 3;
-  const double a = (qi & 1) ? cs : sn, b = (qi & 1) ? sn : cs;
-  s = qi >= 2 ? -a : a;
-  c = (qi == 1 || qi == 2) ? -b : b;
+  const bool odd = qi & 1u;
+  const double a = odd ? cs : sn, b = odd ? sn : cs;
+  s = flip_sign(a, qi << 30);
+  c = flip_sign(b, (qi + 1u) << 30);
 }
 __device__ __forceinline__ void sincos_2pi(float x, float& s, float& c) { sincospif(2.0f * x, &s, &c); }
 
@@ -648,11 +721,11 @@ __device__ __forceinline__ double f_ww_double(const PhysConst& c, const double* 
       l1 = x[9] * L;
       l2 = L - l1;
     }
-    const double tau = exp(L);
+    const double tau = exp_fin(L);
     sh = tau * c.S;
     rs = sqrt_nr(sh);
     rho_rng = atan_rr((sh - c.M2) * c.invMG) - c.rho_lo;
-    lum = 2.0 * (tau * c.Ldiff) * (-L) * pdf_pair(c, tau, L, expm1(l1) * expm1(l2));
+    lum = tau * -L * pdf_pair(c, tau, L, expm1_fin(l1) * expm1_fin(l2));
   }
   // the masses from the Breit-Wigner maps; their Jacobians' resonance factors cancel
   // the W propagators (see ww_me2): only the maps' ranges enter the weight
@@ -668,17 +741,16 @@ __device__ __forceinline__ double f_ww_double(const PhysConst& c, const double* 
   const double lam = (sh - mp2 - mm2) * (sh - mp2 - mm2) - 4.0 * mp2 * mm2;
   if (!(lam > 0.0)) return 0.0;
   const double sl = sqrt_nr(lam);
-  const double gbw = (c.gs * c.gs) * c.invMG;
   const double ct = 2.0 * x[2] - 1.0, st = sqrt_nr((1.0 - ct) * (1.0 + ct));
   // s-channel photon + Z coefficients, left-handed quark [q], and the sum of the squares
   // of the right-handed ones; hadronic: e^2 Q / shat + e^2 f (shat - MZ^2 - i MZ GZ) /
   // |shat - MZ^2 + i MZ GZ|^2, the two reciprocals from one
   double cre[2] = {c.cs_re[0][0], c.cs_re[1][0]}, cim[2] = {c.cs_im[0][0], c.cs_im[1][0]}, csR2 = c.csR2;
-  double ish;
+  double wk = c.wk;
   if constexpr (HAD) {
     const double dr = sh - c.mz2, dd = dr * dr + c.mzgz2, r = rcp_nr(sh * dd);
-    const double idd = r * sh;
-    ish = r * dd;
+    const double idd = r * sh, ish = r * dd;
+    wk *= ish;
     csR2 = 0.0;
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
@@ -687,10 +759,8 @@ __device__ __forceinline__ double f_ww_double(const PhysConst& c, const double* 
       const double rr = c.csq[q] * ish + c.csf[q][1] * dr * idd, ri = -c.csf[q][1] * c.mzgz * idd;
       csR2 += rr * rr + ri * ri;
     }
-  } else {
-    ish = 1.0 / sh;
   }
-  const double i2rs = HAD ? 0.5 * rcp_nr(rs) : 1.0 / (2.0 * rs);
+  const double i2rs = HAD ? 0.5 * rcp_nr(rs) : c.i2rs;
   const double q = sl * i2rs;
   // E+ + E- = rs as rounded: the diagrams cancel by (shat / M_W^2)^2 at high energy, and
   // a mismatch of the energies would come through (measured on 1e5 hadronic events: the
@@ -737,7 +807,7 @@ __device__ __forceinline__ double f_ww_double(const PhysConst& c, const double* 
   const double P = tu * td, N = (mep * xp) * (mem * xm);
   const double r = rcp_nr(P * N), iP = r * N, iN = r * P;
   const double me = ww_spinor_me2(c, w, l3, n4, n5, l6, cre, cim, csR2, -c.ct * (iP * td), -c.ct * (iP * tu));
-  const double f = (c.conv * kWWPS) * (gbw * gbw) * ish * (sl * me) * (iN * iN) * (rho_rng * rrng2);
+  const double f = wk * (sl * me) * (iN * iN) * (rho_rng * rrng2);
   if constexpr (HAD) return f * lum;
   return f;
 }
@@ -761,7 +831,7 @@ __device__ __forceinline__ double f_ww_single(const PhysConst& c, const double* 
   const double lam = (sh - mp2 - mm2) * (sh - mp2 - mm2) - 4.0 * mp2 * mm2;
   if (!(lam > 0.0)) return 0.0;
   const double sl = sqrt_nr(lam);
-  const double i2rs = 1.0 / (2.0 * rs);
+  const double i2rs = c.i2rs;
   const double q = sl * i2rs;
   const double Ep = (sh + mp2 - mm2) * i2rs, Em = (sh - mp2 + mm2) * i2rs;
   const double ct = 2.0 * x[2] - 1.0, st = sqrt_nr((1.0 - ct) * (1.0 + ct));

@@ -1713,7 +1713,7 @@ int validate(const vegas_config* c, int64_t max_events) {
 
 // configuration-wide constants, computed once on the host
 PhysConst make_consts(const vegas_config* c, const double* p) {
-  PhysConst k;
+  PhysConst k{};
   std::memset(&k, 0, sizeof(k));
   k.process = c->process;
   k.ndim = c->ndim;
@@ -1770,10 +1770,15 @@ PhysConst make_consts(const vegas_config* c, const double* p) {
     for (int q = 0; q < 2; ++q) {
       const double Q = q == 0 ? 2.0 / 3.0 : -1.0 / 3.0, T3 = q == 0 ? 0.5 : -0.5;
       const double gq[2] = {(T3 - Q * sw2) / (sw * cw), -Q * sw / cw};
-      k.qql[q] = -Q;
       for (int h = 0; h < 2; ++h)
-        for (int hp = 0; hp < 2; ++hp) k.gg[q][2 * h + hp] = gq[h] * gl[hp];
+        for (int hp = 0; hp < 2; ++hp) {
+          const double gg = gq[h] * gl[hp];
+          k.dyA += Q * Q;
+          k.dyB -= 2.0 * Q * gg;  // Q_l = -1
+          k.dyC += gg * gg;
+        }
     }
+    k.wk = k.conv * k.rho_rng * k.invMG * k.invS * k.e4_12 / (8.0 * kPi);
   } else if (c->process == VEGAS_W_PLUS) {
     k.M2 = MW * MW;
     k.MG = MW * GW;
@@ -1788,6 +1793,7 @@ PhysConst make_consts(const vegas_config* c, const double* p) {
     k.ptmin2 = p[VEGAS_P_PTMIN] * p[VEGAS_P_PTMIN];
     const double th = std::tanh(p[VEGAS_P_ETAMAX]);
     k.th2 = th * th;
+    k.wk = k.conv * k.rho_rng * k.invMG * 0.5 * k.g4v2_24 / (8.0 * kPi);
   } else if (c->process == VEGAS_WW_4L || c->process == VEGAS_WW_HAD) {
     k.M2 = MW * MW;
     k.MG = MW * GW;
@@ -1799,7 +1805,10 @@ PhysConst make_consts(const vegas_config* c, const double* p) {
     k.rho_lo = std::atan(k.tlo);
     k.rho_rng = std::atan((k.shat - MW * MW) / k.MG) - k.rho_lo;
     k.gs = std::sqrt(g2) / std::sqrt(2.0);
+    k.i2rs = 1.0 / (2.0 * rs);
     k.ct = -0.5 * g2;
+    const double gbw = (k.gs * k.gs) * k.invMG;
+    k.wk = (k.conv * kWWPS) * (gbw * gbw) / k.shat;
     // Cs = e^2 (Q/shat + gZ (cw/sw) / (shat - MZ^2 + i MZ GZ))
     const double dr = k.shat - MZ * MZ, di = MZ * GZ, dd = dr * dr + di * di;
     double csr2 = 0.0;
@@ -1821,6 +1830,7 @@ PhysConst make_consts(const vegas_config* c, const double* p) {
       k.Lhi = Lhi;
       k.Lrng = Llo - Lhi;
       k.Ldiff = Lhi - Llo;
+      k.wk = (k.conv * kWWPS) * (gbw * gbw) * 2.0 * k.Ldiff;  // 1 / shat is the event's
       k.mz2 = MZ * MZ;
       k.mzgz = MZ * GZ;
       for (int q = 0; q < 2; ++q) {
