@@ -344,18 +344,38 @@ __device__ __forceinline__ void fold_row3(long long lo, long long hi, long long*
   r[2 * stride] = hi >> 16;
 }
 
-// per-lane sums -> wave totals -> the block's S1, S2 columns (call with the whole block)
-__device__ __forceinline__ void fold_sums_to_lds(const long long ls[kFoldLane], long long* acc) {
-  long long t[kFoldLane], r[kLane];
+// a block's per-lane sums, [total][lane] in LDS: the waves add theirs lane by lane, then one
+// wave per total sums its 64 slots.  (Each wave summing its own lanes, five sums of six
+// dependent 64-bit steps in every wave, took 2.3 us at the end of a 16-wave block.)
+constexpr int kRedMax = kFoldLane;  // the row of the largest |w|
+struct BlockSums {
+  unsigned long long v[kFoldLane + 1][kWave];
+};
+
+// total k (a wave's share of 48-bit digits, weight 2^(48 (k mod 2)), the fifth 2^96 of w^2)
+// -> the S1, S2 columns, by lane 0: the two 32-bit digits it reaches
+__device__ __forceinline__ void fold_total(int k, long long t, long long* acc) {
+  const bool high = k & 1, top = k == kFoldLane - 1;
+  const int col = (k < 2 ? 0 : kD1) + (top ? 3 : high ? 1 : 0);
+  const long long lo = top ? t : high ? (t & 0xffff) << 16 : t & static_cast<long long>(kMask32);
+  const long long up = high ? t >> 16 : t >> 32;
+  unsigned long long* p = reinterpret_cast<unsigned long long*>(acc) + col;
+  atomicAdd(p, static_cast<unsigned long long>(lo));
+  if (!top) atomicAdd(p + 1, static_cast<unsigned long long>(up));
+}
+
+// per-lane sums -> the block's S1, S2 columns; the slots are zero before and after (call
+// with the whole block; a barrier between the two steps, one before the columns are read)
+__device__ __forceinline__ void fold_sums_add(const long long ls[kFoldLane], BlockSums& red) {
 #pragma unroll
-  for (int k = 0; k < kFoldLane; ++k) t[k] = wave_sum_i64(ls[k]);
-  fold_row3(t[0], t[1], r, 1);
-  fold_row3(t[2], t[3], r + kD1, 1);
-  r[kD1 + 3] = t[4];
-  if ((threadIdx.x & 63) == 0) {
-    unsigned long long* p = reinterpret_cast<unsigned long long*>(acc);
-#pragma unroll
-    for (int k = 0; k < kLane; ++k) atomicAdd(p + k, static_cast<unsigned long long>(r[k]));
+  for (int k = 0; k < kFoldLane; ++k) atomicAdd(&red.v[k][threadIdx.x & (kWave - 1)], static_cast<unsigned long long>(ls[k]));
+}
+__device__ __forceinline__ void fold_sums_to_lds(BlockSums& red, long long* acc) {
+  const int lane = threadIdx.x & (kWave - 1);
+  for (int k = threadIdx.x / kWave; k < kFoldLane; k += blockDim.x / kWave) {
+    const long long t = wave_sum_i64(static_cast<long long>(red.v[k][lane]));
+    red.v[k][lane] = 0;
+    if (lane == 0) fold_total(k, t, acc);
   }
 }
 
@@ -444,7 +464,21 @@ __global__ __launch_bounds__(MAXT) void k_event(EventArgs a) {
   const int fcol_h = fold_cols(nslot), fcol = fcol_h + (OBS ? fold_obs_cols(a.nobs) : 0);
   double* e_lds = reinterpret_cast<double*>(smem);
   long long* acc = reinterpret_cast<long long*>(e_lds + nd * (n + 1));  // FUSED: [fcol]
-  for (int i = threadIdx.x; i < nd * (n + 1); i += blockDim.x) e_lds[i] = a.b.edges[i];
+  // the grid, four loads in flight per lane (one after the other they were most of the 2 us
+  // before a W+W- block's first event)
+  for (int i = threadIdx.x; i < nd * (n + 1); i += 4 * blockDim.x) {
+    double t[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int q = i + k * blockDim.x;
+      t[k] = q < nd * (n + 1) ? a.b.edges[q] : 0.0;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int q = i + k * blockDim.x;
+      if (q < nd * (n + 1)) e_lds[q] = t[k];
+    }
+  }
   if constexpr (FUSED)
     for (int i = threadIdx.x; i < fcol; i += blockDim.x) acc[i] = 0;
   // with 10 or more dimensions the register budget of 2 waves per SIMD is spent on the
@@ -461,9 +495,13 @@ __global__ __launch_bounds__(MAXT) void k_event(EventArgs a) {
     // by its finalisation, earlier on the stream)
     for (int i = threadIdx.x; i < ncol; i += blockDim.x) a.b.acc_tot[i] = 0;
   }
+  __shared__ BlockSums red;
+  for (int i = threadIdx.x; i < (kFoldLane + 1) * kWave; i += blockDim.x) (&red.v[0][0])[i] = 0;
   __shared__ uint32_t draw;  // the block's next chunk of 64 events that no wave has taken
   const uint32_t nwave = blockDim.x / kWave;
+  __shared__ uint32_t blk[2];  // non-zero and non-finite weights
   if (threadIdx.x == 0) draw = nwave;
+  if (threadIdx.x < 2) blk[threadIdx.x] = 0u;
   int E1 = 0, E2 = 0;
   if constexpr (FUSED) {
     E1 = a.b.fxs[1];
@@ -606,11 +644,12 @@ __global__ __launch_bounds__(MAXT) void k_event(EventArgs a) {
           lsum[k * lsn + threadIdx.x] = 0;
         }
       first = __builtin_amdgcn_readfirstlane(lim + threadIdx.x / kWave);
-      fold_sums_to_lds(ls, acc);
+      fold_sums_add(ls, red);
 #pragma unroll
       for (int k = 0; k < kFoldLane; ++k) ls[k] = 0;
       __syncthreads();  // the histogram is whole, and no wave draws
       if (threadIdx.x == 0) draw = lim + nwave;
+      fold_sums_to_lds(red, acc);
       lim = min(mine, lim + kFoldEvents / kWave);
       for (int q = threadIdx.x; q < nslot; q += blockDim.x) fold_carry(acc + hist_col(q), nslot);
       if constexpr (OBS)
@@ -619,25 +658,27 @@ __global__ __launch_bounds__(MAXT) void k_event(EventArgs a) {
     }
   }
   // block totals (LDS) -> one device-wide atomic per block and quantity
-  __shared__ unsigned long long blk[3];
-  if (threadIdx.x < 3) blk[threadIdx.x] = 0ull;
-  __syncthreads();
-  wmax = wave_max_u64(wmax);
-  if ((threadIdx.x & (kWave - 1)) == 0) {
-    atomicMax(&blk[0], wmax);
-    atomicAdd(&blk[1], static_cast<unsigned long long>(nz));
-    atomicAdd(&blk[2], static_cast<unsigned long long>(nnf));
-  }
+  const int lane = threadIdx.x & (kWave - 1);
   if constexpr (kLdsSums)
 #pragma unroll
     for (int k = 0; k < kFoldLane; ++k) ls[k] = lsum[k * lsn + threadIdx.x];
-  if constexpr (FUSED) fold_sums_to_lds(ls, acc);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    if (blk[0]) atomicMax(&a.b.maxw[0], blk[0]);
-    if (blk[1]) atomicAdd(&a.b.cnt[0], blk[1]);
-    if (blk[2]) atomicAdd(&a.b.cnt[1], blk[2]);
+  if constexpr (FUSED) fold_sums_add(ls, red);
+  atomicMax(&red.v[kRedMax][lane], wmax);
+  if (lane == 0) {
+    if (nz) atomicAdd(&blk[0], nz);
+    if (nnf) atomicAdd(&blk[1], nnf);
   }
+  __syncthreads();
+  if constexpr (FUSED) fold_sums_to_lds(red, acc);
+  if (threadIdx.x / kWave == nwave - 1) {
+    wmax = wave_max_u64(red.v[kRedMax][lane]);
+    if (lane == 0) {
+      if (wmax) atomicMax(&a.b.maxw[0], wmax);
+      if (blk[0]) atomicAdd(&a.b.cnt[0], static_cast<unsigned long long>(blk[0]));
+      if (blk[1]) atomicAdd(&a.b.cnt[1], static_cast<unsigned long long>(blk[1]));
+    }
+  }
+  __syncthreads();
   if constexpr (FUSED) {
     long long* row = a.b.part_acc + static_cast<int64_t>(blockIdx.x) * part_ld(ncol);
     if (threadIdx.x < kColHist) row[threadIdx.x] = acc[threadIdx.x];
