@@ -15,7 +15,7 @@
 //   k_finalize  one block: totals -> d, S1, S2 as doubles, I_j and var_j; re-folds
 //               from the records if this iteration's max |w| left the window of
 //               the previous scale, and fixes the next iteration's scales.
-//   k_refine    (vegas_refine) one 64-lane block per dimension: smoothing,
+//   k_refine    (vegas_refine) one block per dimension: smoothing,
 //               damping, equal-importance rebinning.
 // Integer accumulation is associative, so every launch configuration gives
 // byte-identical results (the paper's independence from the thread count,
@@ -64,6 +64,7 @@ constexpr int kObsLd = VEGAS_MAX_OBS_BINS + 2;
 constexpr int kStrataBlocks = 1024;  // blocks of the hypercube fold (rows of its partials)
 constexpr int kDirectRowsMax = 64;   // up to this many partial rows the finalisation sums them itself
 constexpr int kFinThreads = 1024;    // finalisation block when it folds or refines (else 256)
+constexpr int kRefineThreads = 256;  // threads that refine one dimension
 
 // n / d for n < 2^31 by multiply and shift: with l = ceil(log2 d), M = floor(2^(32+l) / d)
 // + 1 < 2^33 gives floor(n M / 2^(32+l)) = floor(n / d) exactly, and n M < 2^64
@@ -1154,8 +1155,8 @@ __device__ __forceinline__ double iteration_variance(const FinArgs& f, double S1
   return fma(-I, I, S2 / N) / (N - 1.0);
 }
 
-__device__ __forceinline__ void refine_dim(bool active, bool preloaded, int n, double alpha, const double* hist,
-                                           const double* e_in, double* e_out, double* sm);
+__device__ __forceinline__ void refine_dim(bool active, bool preloaded, int t, int G, int n, double alpha,
+                                           const double* hist, const double* e_in, double* e_out, double* sm);
 
 // OBS: an observable histogram is set (f.nobs > 0); the plain variant carries none of its code
 template <bool OBS>
@@ -1408,10 +1409,10 @@ __device__ __forceinline__ void finalize_block(const FinArgs& f, unsigned char* 
     // has to swap the grid buffers (the same routine as k_refine: the same bits)
     // (the histogram and the old grid are already in the scratch; refine_dim's first
     // barrier orders those LDS writes before its reads)
-    const int d = d_lo + (threadIdx.x >> 6);
+    const int G = d_hi - d_lo == 1 ? kRefineThreads : kWave, d = d_lo + static_cast<int>(threadIdx.x) / G;
     const bool active = d < d_hi;
-    refine_dim(active, true, n, f.alpha, nullptr, nullptr, b.edges_alt + (active ? d : 0) * (n + 1),
-               rsm + (active ? d - d_lo : 0) * 4 * (n + 1));
+    refine_dim(active, true, threadIdx.x & (G - 1), G, n, f.alpha, nullptr, nullptr,
+               b.edges_alt + (active ? d : 0) * (n + 1), rsm + (active ? d - d_lo : 0) * 4 * (n + 1));
   }
 }
 
@@ -1450,19 +1451,8 @@ __global__ void k_finalize(FinArgs f) {
 }
 
 // ---------------------------------------------------------------------------
-// K4: grid refinement, one single-wave block per dimension
+// K4: grid refinement, one block per dimension
 // ---------------------------------------------------------------------------
-
-// Refinement of dimension d by one wave (lane = threadIdx.x % 64) with LDS scratch
-// sm[4 (n + 1)]; every wave of the block calls it (its one barrier is block-wide);
-// active == false only keeps the barrier.  Reads the histogram hist[n] and edges
-// e_in[n + 1] (or finds them already in sm[0..n) and sm[3 (n + 1) ..] when preloaded),
-// writes e_out[n + 1] (may equal e_in).  An empty histogram keeps the dimension's grid.
-// Lane l owns the bins [c l, c l + c), c = ceil(n / 64) <= 4: after the barrier the
-// smoothing, the damping, the cumulative importance and the new edges stay in its
-// registers, with wave sums and one wave scan by DPP; each lane places the new edges
-// that fall into its own bins (edge k lies in the old bin j with cm[j] < k stp <= cm[j+1],
-// the same bin a search over cm finds), so no cross-lane search is needed.
 __device__ __forceinline__ double wave_scan_f64(double v) {  // inclusive, lanes 0..63
   v += dpp_f64<0x111, 0xf, true>(v);
   v += dpp_f64<0x112, 0xf, true>(v);
@@ -1483,117 +1473,112 @@ __device__ __forceinline__ double wave_scan_max_f64(double v) {  // inclusive, f
   return v;
 }
 
-__device__ __forceinline__ double read_lane_f64(double v, int lane) {  // lane wave-uniform
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane(static_cast<int>(b), lane);
-  const int hi = __builtin_amdgcn_readlane(static_cast<int>(b >> 32), lane);
-  return __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<unsigned int>(lo));
-}
-
-__device__ __forceinline__ void refine_dim(bool active, bool preloaded, int n, double alpha, const double* hist,
-                                           const double* e_in, double* e_out, double* sm) {
+// Refinement of one dimension by G threads (whole waves, t = 0 .. G - 1 of them) with LDS
+// scratch sm[4 (n + 1)]; every thread of the block calls it (its barriers are block-wide);
+// active == false only keeps the barriers.  Reads the histogram hist[n] and edges
+// e_in[n + 1] (or finds them already in sm[0..n) and sm[3 (n + 1) ..] when preloaded),
+// writes e_out[n + 1] (may equal e_in).  An empty histogram keeps the dimension's grid.
+// A thread smooths and damps one bin and places one new edge (edge k lies in the old bin j
+// with cm[j] < k stp <= cm[j + 1], found by bisection); the sums and the scan between take
+// one wave, whose lane l owns the bins [c l, c l + c), c = ceil(n / 64) <= 4, so the bits
+// do not depend on G.  Bound by latency: with two bins and all the edges in them per lane
+// of a single wave it was 3.5 of a finalisation's 8.4 us, now 2.0.
+__device__ __forceinline__ void refine_dim(bool active, bool preloaded, int t, int G, int n, double alpha,
+                                           const double* hist, const double* e_in, double* e_out, double* sm) {
   double* hs = sm;                // histogram of this dimension
+  double* m = sm + (n + 1);       // smoothed histogram, then importance
+  double* cm = sm + 2 * (n + 1);  // cumulative importance at the bin edges
   double* eo = sm + 3 * (n + 1);  // old edges
-  const int lane = threadIdx.x & 63;
+  const int lane = t & (kWave - 1);
   if (active && !preloaded) {
-    for (int k = lane; k < n; k += kWave) hs[k] = hist[k];
-    for (int k = lane; k <= n; k += kWave) eo[k] = e_in[k];
+    for (int k = t; k < n; k += G) hs[k] = hist[k];
+    for (int k = t; k <= n; k += G) eo[k] = e_in[k];
   }
   __syncthreads();
+  if (active)
+    for (int k = t; k < n; k += G)
+      m[k] = k == 0       ? (hs[0] + hs[1]) * 0.5
+             : k == n - 1 ? (hs[n - 2] + hs[n - 1]) * 0.5
+                          : div_nr(hs[k - 1] + hs[k] + hs[k + 1], 3.0);
+  __syncthreads();
   const int c = (n + kWave - 1) / kWave, j0 = c * lane;
-  // smoothed histogram of the lane's bins, and the sums of the raw and smoothed ones
-  double v[4];
+  // the sums of the raw and smoothed histograms, in every wave
   double s = 0.0, sb = 0.0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int k = j0 + i;
-    v[i] = 0.0;
-    if (active && i < c && k < n) {
-      double t;
-      if (k == 0) t = (hs[0] + hs[1]) / 2.0;
-      else if (k == n - 1) t = (hs[n - 2] + hs[n - 1]) / 2.0;
-      else t = (hs[k - 1] + hs[k] + hs[k + 1]) / 3.0;
-      v[i] = t;
+  if (active)
+    for (int k = j0; k < j0 + c && k < n; ++k) {
       s += hs[k];
-      sb += t;
+      sb += m[k];
     }
-  }
   s = wave_total_f64(s);
   sb = wave_total_f64(sb);
-  const bool work = active && s > 0.0;  // wave-uniform
+  const bool work = active && s > 0.0;  // uniform over the G threads
+  __syncthreads();
   if (work) {
-    // damped importance m of each bin (the usual damping exponent 1.5 without pow)
+    // damped importance of each bin (the usual damping exponent 1.5 without pow)
     const double isb = 1.0 / sb;
-    double m[4];
+    for (int k = t; k < n; k += G) {
+      const double r = m[k] * isb;
+      double v = r;  // r == 0 and r == 1 stay
+      if (r != 1.0 && r != 0.0) {
+        const double y = div_nr(r - 1.0, r >= 0x1p-1022 && r < 1.0 ? log_pos(r) : log(r));
+        v = alpha == 1.5 ? y * sqrt_nr(y) : pow(y, alpha);
+      }
+      m[k] = v;
+    }
+  }
+  __syncthreads();
+  if (work && t < kWave) {
+    // cumulative importance at the lane's bin edges: the lane's sums r from the scan's
+    // exclusive value, raised to the largest chunk end of the lanes before it (a maximum
+    // is exact, so the lane after this one starts where this one ends, bit for bit): cm is
+    // non-decreasing, and the bins' intervals (cm[j], cm[j+1]] tile (0, cm[n]] whatever
+    // the sums' rounding
     double part = 0.0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      m[i] = 0.0;
-      if (i < c && j0 + i < n) {
-        const double r = v[i] * isb;
-        if (r == 1.0) {
-          m[i] = 1.0;
-        } else if (r != 0.0) {
-          const double y = (r - 1.0) / log(r);
-          m[i] = alpha == 1.5 ? y * sqrt(y) : pow(y, alpha);
-        }
-        part += m[i];
-      }
+    for (int k = j0; k < j0 + c && k < n; ++k) part += m[k];
+    double r = wave_scan_f64(part) - part, end = r;
+    for (int k = j0; k < j0 + c && k < n; ++k) end += m[k];
+    const double carry = wave_scan_max_f64(dpp_f64<0x138, 0xf, true>(end));  // lanes before (wave_shr:1)
+    if (j0 < n) cm[j0] = carry;
+    for (int k = j0; k < j0 + c && k < n; ++k) {
+      r += m[k];
+      if (k + 1 < j0 + c || k + 1 == n) cm[k + 1] = fmax(r, carry);
     }
-    // cumulative importance at the lane's bin edges, cm[j0 + i] = cb[i]: the lane's sums
-    // r from the scan's exclusive value, raised to the largest chunk end of the lanes
-    // before it (a maximum is exact, so the lane after this one sees this lane's top
-    // cb[c] as its cb[0], bit for bit): cm is non-decreasing across lanes, and the
-    // bins' intervals (cm[j], cm[j+1]] tile (0, cm[n]] whatever the sums' rounding
-    double r[5];
-    r[0] = wave_scan_f64(part) - part;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) r[i + 1] = (i < c && j0 + i < n) ? r[i] + m[i] : r[i];
-    const double carry = wave_scan_max_f64(dpp_f64<0x138, 0xf, true>(r[4]));  // lanes before (wave_shr:1)
-    double cb[5];
-    cb[0] = carry;
-#pragma unroll
-    for (int i = 1; i < 5; ++i) cb[i] = fmax(r[i], carry);
-    const double stp = read_lane_f64(cb[4], (n - 1) / c) / n;  // cm[n] / n
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int j = j0 + i;
-      if (i >= c || j >= n) break;
-      const double lo = cb[i], hi = cb[i + 1];
-      // the first interior edge above lo
-      int k = static_cast<int>(lo / stp);
-      k = k < 1 ? 1 : k;
-      while (k > 1 && (k - 1) * stp > lo) --k;
-      while (k < n && k * stp <= lo) ++k;
-      if (k >= n) continue;
-      const double e0 = eo[j], e1 = eo[j + 1];
-      for (; k < n; ++k) {
-        const double target = k * stp;
-        if (j < n - 1 && target > hi) break;  // the last bin takes every remaining edge
-        double frac = m[i] > 0.0 ? (target - lo) / m[i] : 0.0;
-        frac = frac < 0.0 ? 0.0 : (frac > 1.0 ? 1.0 : frac);
-        e_out[k] = e0 + frac * (e1 - e0);
+  }
+  __syncthreads();
+  if (work) {
+    const double stp = cm[n] / n;
+    for (int k = t; k <= n; k += G) {
+      if (k == 0 || k == n) {
+        e_out[k] = k ? 1.0 : 0.0;
+        continue;
       }
-    }
-    if (lane == 0) {
-      e_out[0] = 0.0;
-      e_out[n] = 1.0;
+      const double target = __dmul_rn(static_cast<double>(k), stp);
+      int lo = 0, hi = n - 1;  // the last bin below whose upper edge it lies
+      while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        const bool right = cm[mid] < target;
+        lo = right ? mid : lo;
+        hi = right ? hi : mid - 1;
+      }
+      double frac = m[lo] > 0.0 ? (target - cm[lo]) / m[lo] : 0.0;
+      frac = frac < 0.0 ? 0.0 : (frac > 1.0 ? 1.0 : frac);
+      e_out[k] = __fma_rn(frac, eo[lo + 1] - eo[lo], eo[lo]);
     }
   } else if (active && e_out != e_in) {
-    for (int k = lane; k <= n; k += kWave) e_out[k] = eo[k];
+    for (int k = t; k <= n; k += G) e_out[k] = eo[k];
   }
 }
 
-// one 64-lane block per dimension, in place
+// one block per dimension, in place
 __global__ void k_refine(DevBufs b, int nbins, double alpha) {
   extern __shared__ unsigned char smem[];
   const int d = blockIdx.x, n = nbins;
   double* e = b.edges + d * (n + 1);
-  refine_dim(true, false, n, alpha, b.hist + d * n, e, e, reinterpret_cast<double*>(smem));
+  refine_dim(true, false, threadIdx.x, blockDim.x, n, alpha, b.hist + d * n, e, e, reinterpret_cast<double*>(smem));
 }
 
 // ---------------------------------------------------------------------------
-// K5: inverse-variance combination over the iterations
+// read-backs, and K5: inverse-variance combination over the iterations
 // ---------------------------------------------------------------------------
 // a read-back's way to the host: pinned host memory that the device writes itself, the
 // values and then a sequence number that the host waits for
@@ -2830,7 +2815,7 @@ int vegas_refine(vegas_handle h) {
     std::swap(h->b.edges, h->b.edges_alt);
   } else {
     TimedLaunch t(h, 3);
-    hipExtLaunchKernelGGL(k_refine, dim3(h->D), dim3(kWave), sizeof(double) * 4 * (h->n + 1), h->stream, t.e0,
+    hipExtLaunchKernelGGL(k_refine, dim3(h->D), dim3(kRefineThreads), sizeof(double) * 4 * (h->n + 1), h->stream, t.e0,
                           t.e1, 0, h->b, h->n, h->cfg.alpha);
     VG_HIP(t.done());
   }
