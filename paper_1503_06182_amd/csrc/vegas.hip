@@ -881,28 +881,48 @@ __global__ __launch_bounds__(256) void k_strata_adapt(DevBufs b, int64_t H, cons
 constexpr int kAllocThreads = 256;
 constexpr int kAllocBlocksMax = 1024;
 
+// block sums, in the order of a halving tree (thread t + s to thread t, s = 128, 64 in LDS,
+// then 32 .. 1 in the first wave): two barriers, where a tree in LDS took nine
 __device__ double block_sum_fixed(double v, double* red) {
-  red[threadIdx.x] = v;
+  static_assert(kAllocThreads == 4 * kWave);
+  const int t = threadIdx.x;
+  red[t] = v;
   __syncthreads();
-  for (int st = kAllocThreads / 2; st > 0; st >>= 1) {
-    if (static_cast<int>(threadIdx.x) < st) red[threadIdx.x] += red[threadIdx.x + st];
-    __syncthreads();
+  if (t < kWave) {
+    v = (red[t] + red[t + 2 * kWave]) + (red[t + kWave] + red[t + 3 * kWave]);
+#pragma unroll
+    for (int st = kWave / 2; st > 0; st >>= 1) v += __shfl_down(v, st, kWave);
+    if (t == 0) red[0] = v;
   }
+  __syncthreads();
   const double r = red[0];
   __syncthreads();
   return r;
 }
 
 __device__ long long block_sum_int(long long v, long long* red) {
-  red[threadIdx.x] = v;
+  v = wave_sum_i64(v);
+  if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = v;
   __syncthreads();
-  for (int st = kAllocThreads / 2; st > 0; st >>= 1) {
-    if (static_cast<int>(threadIdx.x) < st) red[threadIdx.x] += red[threadIdx.x + st];
-    __syncthreads();
-  }
-  const long long r = red[0];
+  const long long r = red[0] + red[1] + red[2] + red[3];
   __syncthreads();
   return r;
+}
+
+// exclusive sum over the threads before this one
+__device__ int block_scan_int(int v, int* red) {
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  int x = v;
+#pragma unroll
+  for (int st = 1; st < kWave; st <<= 1) {
+    const int y = __shfl_up(x, st, kWave);
+    if (lane >= st) x += y;
+  }
+  if (lane == kWave - 1) red[wave] = x;
+  __syncthreads();
+  int before = 0;
+  for (int w = 0; w < wave; ++w) before += red[w];
+  return before + x - v;
 }
 
 // sum of p over all blocks' partials, in the same order in every block
@@ -930,7 +950,7 @@ __global__ __launch_bounds__(kAllocThreads) void k_strata_alloc_f(const double* 
                                                                    long long* partf, int64_t H, int64_t C, int G,
                                                                    int64_t freev) {
   __shared__ double red[kAllocThreads];
-  __shared__ long long lred[kAllocThreads];
+  __shared__ long long lred[kAllocThreads / kWave];
   const double A = alloc_total(part, G, red);
   const int64_t h0 = static_cast<int64_t>(blockIdx.x) * C, h1 = min(H, h0 + C);
   long long loc = 0;
@@ -948,7 +968,8 @@ __global__ __launch_bounds__(kAllocThreads) void k_strata_alloc_c(int32_t* cnt, 
                                                                    const long long* partf, int64_t H, int64_t C,
                                                                    int G, int64_t freev) {
   __shared__ double red[kAllocThreads];
-  __shared__ long long lred[kAllocThreads];
+  __shared__ long long lred[kAllocThreads / kWave];
+  __shared__ int ired[kAllocThreads / kWave];
   const double A = alloc_total(part, G, red);
   long long F = 0;
   for (int k = threadIdx.x; k < G; k += kAllocThreads) F += partf[k];
@@ -968,26 +989,15 @@ __global__ __launch_bounds__(kAllocThreads) void k_strata_alloc_c(int32_t* cnt, 
   const int64_t h0 = static_cast<int64_t>(blockIdx.x) * C, h1 = min(H, h0 + C);
   const int64_t sub = (h1 - h0 + kAllocThreads - 1) / kAllocThreads;
   const int64_t s0 = min(h1, h0 + static_cast<int64_t>(threadIdx.x) * sub), s1 = min(h1, s0 + sub);
-  long long loc = 0;
+  int loc = 0;  // the events of an iteration fit 31 bits
   for (int64_t h = s0; h < s1; ++h) {
     const int32_t c = static_cast<int32_t>(2 + (equal ? q : cnt[h]) + (h < R ? 1 : 0));
     cnt[h] = c;
     loc += c;
   }
-  lred[threadIdx.x] = loc;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    long long run = start;
-    for (int k = 0; k < kAllocThreads; ++k) {
-      const long long v = lred[k];
-      lred[k] = run;
-      run += v;
-    }
-  }
-  __syncthreads();
-  long long o = lred[threadIdx.x];
+  int o = static_cast<int>(start) + block_scan_int(loc, ired);
   for (int64_t h = s0; h < s1; ++h) {
-    off[h] = static_cast<int32_t>(o);
+    off[h] = o;
     o += cnt[h];
   }
 }
@@ -1026,18 +1036,22 @@ __device__ __forceinline__ int strata_lane_of(int32_t p, int32_t o) {
   return j;
 }
 
-// the hypercube index of every event: cube[off[h] .. off[h] + cnt[h] - 1] = h, one
-// wave per group of 64 hypercubes writing its records 64 at a time
+// the hypercube index of every event: cube[off[h] .. off[h] + cnt[h] - 1] = h.  A block
+// takes a group of 64 hypercubes, its waves the group's records, 2 x 64 at a time.  Bound by
+// the latency of the search's six lane exchanges: a wave per group, 64 records at a time,
+// took 11 us for 1e6 events in 65,536 hypercubes, the fullest group last
 __global__ __launch_bounds__(256) void k_strata_expand(const int32_t* cnt, const int32_t* off, int32_t* cube,
                                                        int64_t H) {
-  const int lane = threadIdx.x & (kWave - 1), wpb = blockDim.x / kWave;
-  const int64_t ngroups = (H + kWave - 1) / kWave, gstep = static_cast<int64_t>(gridDim.x) * wpb;
-  for (int64_t g = static_cast<int64_t>(blockIdx.x) * wpb + threadIdx.x / kWave; g < ngroups; g += gstep) {
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, wpb = blockDim.x / kWave;
+  const int64_t ngroups = (H + kWave - 1) / kWave;
+  for (int64_t g = blockIdx.x; g < ngroups; g += gridDim.x) {
     const StrataGroup s = strata_group(cnt, off, H, g);
-    for (int64_t cb = s.B; cb < s.E; cb += kWave) {
-      const int64_t p = cb + lane;
+    for (int64_t cb = s.B + 2 * kWave * wave; cb < s.E; cb += 2 * kWave * wpb) {
+      const int64_t p = cb + lane, q = p + kWave;
       const int j = strata_lane_of(static_cast<int32_t>(p < s.E ? p : s.E - 1), s.o);
+      const int k = strata_lane_of(static_cast<int32_t>(q < s.E ? q : s.E - 1), s.o);
       if (p < s.E) cube[p] = static_cast<int32_t>(g * kWave + j);
+      if (q < s.E) cube[q] = static_cast<int32_t>(g * kWave + k);
     }
   }
 }
@@ -2623,7 +2637,7 @@ int run_iteration(vegas_handle h, int64_t n_req, const float* ext_y, const float
     hipLaunchKernelGGL(k_strata_alloc_c, dim3(G), dim3(kAllocThreads), 0, h->stream, h->s_cnt, h->s_off, h->s_part,
                        h->s_partf, H, C, G, freev);
     VG_HIP(hipGetLastError());
-    const int64_t xb = std::min<int64_t>((H + 255) / 256, 4096);
+    const int64_t xb = std::min<int64_t>((H + kWave - 1) / kWave, 4096);
     hipLaunchKernelGGL(k_strata_expand, dim3(static_cast<unsigned>(xb)), dim3(256), 0, h->stream, h->s_cnt,
                        h->s_off, h->s_cube, H);
     VG_HIP(hipGetLastError());
