@@ -52,13 +52,13 @@ sys.path.insert(0, ROOT)
 #    x 2 + WRITE_SIZE x 1 KiB, the factors read from a plain 1 GiB device copy).
 # The counter summaries are under profiles/.
 EVENT_KERNEL_WORK = {
-    ("w_plus", "fp64"): {"algorithmic_f64": 341.5, "f64": 325.2, "f32": 0.0, "traffic": 22_169_771,
+    ("w_plus", "fp64"): {"algorithmic_f64": 341.5, "f64": 237.0, "f32": 0.0, "traffic": 15_524_352,
                          "events": 1_000_000},
-    ("ww_4l", "fp64"): {"algorithmic_f64": 813.0, "f64": 1033.7, "f32": 0.0, "traffic": 180_107_630,
+    ("ww_4l", "fp64"): {"algorithmic_f64": 813.0, "f64": 606.0, "f32": 0.0, "traffic": 166_888_346,
                         "events": 10_000_000},
-    ("ww_4l", "fp32me"): {"algorithmic_f64": None, "f64": 636.7, "f32": 418.0, "traffic": None,
+    ("ww_4l", "fp32me"): {"algorithmic_f64": None, "f64": 587.0, "f32": 419.0, "traffic": None,
                           "events": 10_000_000},
-    ("ww_had", "fp64"): {"algorithmic_f64": 1110.0, "f64": 1319.1, "f32": 0.0, "traffic": 216_902_407,
+    ("ww_had", "fp64"): {"algorithmic_f64": 1110.0, "f64": 874.0, "f32": 0.0, "traffic": 225_081_139,
                          "events": 10_000_000},
 }
 # FP64 FLOPs of one call of the library's version of each mathematical function the
@@ -69,10 +69,10 @@ OCML_FLOP_PER_CALL = {"atan": 58.0, "log": 79.0, "exp": 27.0, "expm1": 32.0, "ta
                       "sqrt": 17.0, "div": 14.0}
 # HBM bytes of one histogram-stage launch (k_accsum), from the same counters, at the
 # workload's default event count
-HIST_STAGE_TRAFFIC = {("w_plus", 1_000_000): 10_180_818, ("ww_4l", 10_000_000): 20_433_037}
+HIST_STAGE_TRAFFIC = {("w_plus", 1_000_000): 3_412_787, ("ww_4l", 10_000_000): 6_768_128}
 # FP64 FLOPs of the adjoint's event kernel per (event, parameter point), and its HBM
 # bytes per call at 64 points x 1e6 events, from the same kind of counter runs
-ADJOINT_KERNEL_WORK = {"f64": 264.1, "traffic": 48_201_677, "events": 1_000_000}
+ADJOINT_KERNEL_WORK = {"f64": 69.8, "traffic": 12_184_986, "events": 1_000_000}
 # matrix-core FLOPs of one coupling layer per event: the algorithmic work of the two
 # 128-wide products, 2 x (128 x 128 + 128 x 188) per event (the kernel pads the 188
 # spline parameters to 192 columns; the padding is not counted as work)

@@ -128,7 +128,9 @@ int vegas_workspace_size(const vegas_config *cfg, int64_t max_events, size_t *by
  * library never frees it) or, if workspace is NULL, allocate them itself;
  * set the uniform grid e_k = k / nbins (Sec. 2.1: the grid is then optimised
  * after each iteration).  stream: hipStream_t or NULL for the null stream;
- * the handle is bound to the current device.
+ * the handle is bound to the current device.  Beside the workspace a handle holds
+ * 33 KB of pinned host memory for its read-backs, from a pool that keeps at
+ * most 16 such buffers between handles.
  * Errors: VEGAS_EINVAL, VEGAS_ENOMEM, VEGAS_EHIP. */
 int vegas_init(const vegas_config *cfg, int64_t max_events, void *workspace, size_t ws_bytes,
                void *stream, vegas_handle *out);

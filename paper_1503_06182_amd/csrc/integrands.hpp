@@ -606,7 +606,7 @@ __device__ __forceinline__ R ww_me2(const PhysConst& c, const cx<R> ep[4], const
 // per 64 events and 137 instead of 157 registers: an iteration of 1e7 W+W- events 303 us
 // instead of 378, of 3e6 hadronic ones 196 instead of 221.  (Since then the shorter
 // divisions, roots and sines, and the weight's constant factors formed on the host, have
-// taken it to 838 instructions, and the two iterations to 276 and 172 us.)
+// taken it to 817 instructions, and with all other steps the W+W- iteration to 253 us.)
 // ---------------------------------------------------------------------------
 // light-cone components of the bosons (the W+ along qx, qz): W+ E -+ qz, W- E -+ qz (its
 // momentum is -qx, -qz), each sum of positive terms or the quotient (m^2 + qx^2) over its

@@ -416,8 +416,10 @@ struct EventArgs {
 // ---------------------------------------------------------------------------
 constexpr double kExtLo = 0x1p-40, kExtHi = 1.0 - 0x1p-40;
 
-// (W+W- with four spills 20 bytes a lane and ran the same 1500 us per 5 x 1e7 events; the
-// hadronic W+W- with three spills 52 bytes and took 573 us per 3 x 3e6, with two 581)
+// waves per SIMD that the register allocation must allow (W+W- with four spills 12 bytes a
+// lane: 1302 against 1311 us per 5 x 1e7 events, but 299 against 293 us for the small
+// iterations of the two-stage schedule; the hadronic W+W- with three spills 36 bytes and
+// took 573 us per 3 x 3e6 events when it got them, with two 581)
 template <int PROC>
 constexpr int event_min_waves() {
   return PROC == VEGAS_WW_HAD || PROC == VEGAS_WW_4L ? 3 : 4;
@@ -2103,8 +2105,10 @@ namespace {
 // and synchronisation it then takes are refused by the runtime, as ever)
 MailArgs mail_next(vegas_state* h) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (!h->mail || hipStreamIsCapturing(h->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone)
-    return MailArgs{nullptr, nullptr, 0};
+  if (!h->mail) return MailArgs{nullptr, nullptr, 0};
+  const hipError_t e = hipStreamIsCapturing(h->stream, &cap);
+  if (e != hipSuccess) (void)hipGetLastError();  // the call that follows reports what is wrong
+  if (e != hipSuccess || cap != hipStreamCaptureStatusNone) return MailArgs{nullptr, nullptr, 0};
   return MailArgs{h->mail->data, &h->mail->flag, ++h->mail->seq};
 }
 
