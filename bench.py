@@ -493,7 +493,7 @@ def bench_flow(args, emit=True):
     relvar_f = sum(r["var"] * N / r["I"] ** 2 for r in rf) / len(rf)
     relvar_v = sum(r["var"] * N / r["I"] ** 2 for r in rv) / len(rv)
     # the matrix-core roofline of the sampling layers: Flow.sample of N points (the six
-    # k_flow_layer<true> launches a flow iteration runs), HIP events on the flow's stream
+    # layers of the k_flow_layers<true> launch a flow iteration runs), HIP events on the flow's stream
     zs = torch.rand(N, 8, device="cuda", dtype=torch.float32)
     f.sample(zs)
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
@@ -505,7 +505,7 @@ def bench_flow(args, emit=True):
     torch.cuda.synchronize()
     t_layer = e0.elapsed_time(e1) * 1e-3 / reps / 6
     mfma = FLOW_LAYER_MFMA_FLOP * N / t_layer / 1e12
-    roof = {"kernel": "k_flow_layer<true> (one coupling layer, sampling)", "bound": "mfma", "achieved": mfma,
+    roof = {"kernel": "k_flow_layers<true> (per coupling layer, sampling)", "bound": "mfma", "achieved": mfma,
             "peak": PEAK_BF16_MFMA_TFLOPS, "unit": "TFLOP/s", "frac": mfma / PEAK_BF16_MFMA_TFLOPS,
             "traffic": None, "avg_launch_ms": t_layer * 1e3, "flop_per_event": FLOW_LAYER_MFMA_FLOP}
     del zs

@@ -9,7 +9,7 @@
 //   k_flow_wgrad_part  weight gradients as MFMA contractions over the batch, all layers
 //   k_flow_wgrad_sum   adds the parts; Adam on the FP32 master weights; BF16 copies
 // Batches above kFusedBatch keep one layer's gradients at a time and run layer by layer
-// (k_flow_layer, k_flow_layer_bwd), the same arithmetic.
+// (k_flow_layers, k_flow_layer_bwd), the same arithmetic.
 // Sampling: z uniform (Philox) -> inverse layers 5..0 -> y, log q(y).
 #include <hip/hip_runtime.h>
 
@@ -113,14 +113,23 @@ __device__ __forceinline__ float quad_xor(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, false));
 }
 
-// one coupling layer over a batch; SAMPLE: inverse splines (z -> y), else forward (y -> z).
-// vout may alias vin.  logq[i] += sum of log s' of the four transformed coordinates.
-// Tiles of 64 events; each wave keeps the weight fragments of its output units (W2: 2
-// blocks of 16, W3: 3) for all eight k-steps in registers for the whole launch.
+// the six coupling layers over a batch; SAMPLE: inverse splines (z -> y, layers 5 .. 0), else
+// forward (y -> z, layers 0 .. 5).  Step s reads what step s - 1 wrote (the first reads
+// vfirst) and writes vbuf + s vstride, in place when vstride is 0; vfirst may be vbuf.
+// logq[i] = sum of log s' of the transformed coordinates.  Tiles of 64 events; each wave
+// keeps the weight fragments of its output units (W2: 2 blocks of 16, W3: 3) for all eight
+// k-steps in registers for a layer.
+//
+// An event's layers need no other event, so a block takes its own tiles through all six and
+// no launch separates them: the blocks drift apart, and the last tiles of a layer (4.07 per
+// block at 2e5 events) run beside the next layer's first.  A launch per layer cost 10 us
+// beyond the tiles' time, six times, and the caller's copies and fills: log q of 2e5 points
+// 200 -> 170 us, an iteration of 1e6 sampled events 701 -> 661.  (Loop-invariant addresses
+// are spilled once per layer; the tile loop has no scratch access.)
 template <bool SAMPLE>
-__global__ __launch_bounds__(256, 3) void k_flow_layer(const float* __restrict__ master,
-                                                        const uint16_t* __restrict__ wb, int l, const float* vin,
-                                                        float* vout, float* logq, int64_t B) {
+__global__ __launch_bounds__(256, 3) void k_flow_layers(const float* __restrict__ master,
+                                                         const uint16_t* __restrict__ wb, const float* vfirst,
+                                                         float* vbuf, int64_t vstride, float* logq, int64_t B) {
   // h1 is dead once the second layer has run (a barrier follows it), so the spline
   // parameters the third layer writes share its space: 52 KB per block, 3 blocks per CU
   static_assert(FL_TILE_F * FL_LDQ * sizeof(_Float16) >= FL_TILE_F * FL_LDA * sizeof(uint16_t), "h1 / par union");
@@ -130,89 +139,83 @@ __global__ __launch_bounds__(256, 3) void k_flow_layer(const float* __restrict__
   uint16_t* const h1 = reinterpret_cast<uint16_t*>(h1_par);
   _Float16* const par = h1_par;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const float* m = master + l * FL_LAYER;
-  const uint16_t* w = wb + static_cast<int64_t>(l) * FB_LAYER;
-  bf16x8_t b2[2][FL_HID / 32], b3[3][FL_HID / 32];
-  // second layer: forward, output columns (2 w + cc) 16 + lane % 16; sampling, the units
-  // of the paired-tile order (the lanes of a group receive 8 consecutive units of an event)
-#pragma unroll
-  for (int cc = 0; cc < 2; ++cc) {
-    const int row = SAMPLE ? pair_unit(wave, cc, lane & 15) : (2 * wave + cc) * 16 + (lane & 15);
-#pragma unroll
-    for (int ks = 0; ks < FL_HID / 32; ++ks)
-      b2[cc][ks] = *reinterpret_cast<const bf16x8_t*>(w + FB_W2T + row * FL_HID + ks * 32 + 8 * (lane >> 4));
-  }
-  // third layer: forward, output columns 48 w .. 48 w + 47 in the parameters' order;
-  // sampling, the 47 parameters of coordinate w (the 48th slot takes zero row 188 of the
-  // padded copy), so that wave w's outputs are exactly the parameters of the spline of
-  // coordinate w: tiles 0 and 1 give parameters 0 .. 31 in the paired-tile order,
-  // tile 2 parameters 32 .. 47 in order
-#pragma unroll
-  for (int cc = 0; cc < 3; ++cc) {
-    const int s = lane & 15;
-    const int slot = cc < 2 ? 8 * (s >> 2) + 4 * cc + (s & 3) : 32 + s;
-    const int row = SAMPLE ? (slot < FL_NPAR ? wave * FL_NPAR + slot : FL_NOUT) : 48 * wave + 16 * cc + s;
-#pragma unroll
-    for (int ks = 0; ks < FL_HID / 32; ++ks)
-      b3[cc][ks] = *reinterpret_cast<const bf16x8_t*>(w + FB_W3T + row * FL_HID + ks * 32 + 8 * (lane >> 4));
-  }
-  // biases: forward, of the lane's output column (C = A Bt with the activations as A),
-  // in registers; sampling, of the lane's four output rows (C^T = Bt^T A^T: the
-  // weights are the A operand, so a lane receives four consecutive outputs of one
-  // event, eight over a pair of tiles, stored in one 16-byte write), read from LDS as
-  // the accumulators' initial values (registers held through the splines would spill)
-  __shared__ __align__(16) float bias_s[SAMPLE ? FL_HID + FL_NOUTP : 1];
-  float bias2[2], bias3[3];
-  if constexpr (SAMPLE) {
-    for (int i = tid; i < FL_HID + FL_NOUTP; i += blockDim.x) {
-      const int c = (i - FL_HID) / 48, slot = (i - FL_HID) % 48;
-      bias_s[i] = i < FL_HID ? m[FO_B2 + i] : (slot < FL_NPAR ? m[FO_B3 + c * FL_NPAR + slot] : 0.f);
-    }
-  } else {
-#pragma unroll
-    for (int cc = 0; cc < 2; ++cc) bias2[cc] = m[FO_B2 + (2 * wave + cc) * 16 + (lane & 15)];
-#pragma unroll
-    for (int cc = 0; cc < 3; ++cc) {
-      const int col = (3 * wave + cc) * 16 + (lane & 15);
-      bias3[cc] = col < FL_NOUT ? m[FO_B3 + col] : 0.f;
-    }
-  }
-  const H1Frag u1 = load_h1_frag(m, wave, lane);
+  __shared__ __align__(16) float bias_s[FL_HID + FL_NOUTP];
   const int ri = lane & 15, kq = 4 * (lane >> 4), kq8 = 8 * (lane >> 4);
+  const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
   // thread (event e, slot c) of a tile: its conditioning input c goes to LDS, and it
   // transforms coordinate kFlowX[l][c] after the MLP.  Both inputs of the next tile are
   // loaded while the current one runs (tiles hold disjoint events, so an in-place
   // layer's stores never touch them).
   const int e = tid >> 2, c = tid & 3;
   const int64_t stride = static_cast<int64_t>(gridDim.x) * FL_TILE_F;
-  const int xc = kFlowX[l][c], cc_in = kFlowC[l][c];
-  int64_t e0 = static_cast<int64_t>(blockIdx.x) * FL_TILE_F;
-  float cn = 0.5f, vn = 0.f;
-  if (e0 + e < B) {
-    cn = vin[(e0 + e) * FL_NDIM + cc_in];
-    vn = vin[(e0 + e) * FL_NDIM + xc];
-  }
-  for (; e0 < B; e0 += stride) {
-    const int64_t ev = e0 + e;
-    cond[e][c] = cn;
-    const float vx = vn;
-    if (ev + stride < B) {
-      cn = vin[(ev + stride) * FL_NDIM + cc_in];
-      vn = vin[(ev + stride) * FL_NDIM + xc];
+#pragma unroll 1
+  for (int s = 0; s < FL_NLAYER; ++s) {
+    const int l = SAMPLE ? FL_NLAYER - 1 - s : s;
+    const float* vin = s == 0 ? vfirst : vbuf + (s - 1) * vstride;
+    float* vout = vbuf + s * vstride;
+    const float* m = master + l * FL_LAYER;
+    const uint16_t* w = wb + static_cast<int64_t>(l) * FB_LAYER;
+    bf16x8_t b2[2][FL_HID / 32], b3[3][FL_HID / 32];
+    // second layer: the units of the paired-tile order (the lanes of a group receive 8
+    // consecutive units of an event)
+#pragma unroll
+    for (int cc = 0; cc < 2; ++cc) {
+      const int row = pair_unit(wave, cc, lane & 15);
+#pragma unroll
+      for (int ks = 0; ks < FL_HID / 32; ++ks)
+        b2[cc][ks] = *reinterpret_cast<const bf16x8_t*>(w + FB_W2T + row * FL_HID + ks * 32 + 8 * (lane >> 4));
     }
-    __syncthreads();
-    // the three products run at a raised wave priority and the splines at the base one:
-    // a SIMD then issues the products of one block's waves ahead of another block's
-    // spline work, which keeps the co-resident blocks in different phases, the matrix
-    // cores busy beside the vector ALUs (measured 9 % faster than equal priorities, and
-    // 5 % faster than the reverse order)
-    __builtin_amdgcn_s_setprio(2);
-    mlp_h1(u1, cond, h1, FL_TILE_F);
-    __syncthreads();
-    if constexpr (SAMPLE) {
-      // the bias is the accumulators' initial value (the lane's slots' biases, read
-      // once per layer and tile); ReLU and the bfloat16 rounding on pairs
-      // (v_cvt_pk_bf16_f32, v_pk_max_i16)
+    // third layer: the 47 parameters of coordinate w (the 48th slot takes zero row 188 of the
+    // padded copy), so that wave w's outputs are exactly the parameters of the spline of
+    // coordinate w: tiles 0 and 1 give parameters 0 .. 31 in the paired-tile order,
+    // tile 2 parameters 32 .. 47 in order
+#pragma unroll
+    for (int cc = 0; cc < 3; ++cc) {
+      const int u = lane & 15;
+      const int slot = cc < 2 ? 8 * (u >> 2) + 4 * cc + (u & 3) : 32 + u;
+      const int row = slot < FL_NPAR ? wave * FL_NPAR + slot : FL_NOUT;
+#pragma unroll
+      for (int ks = 0; ks < FL_HID / 32; ++ks)
+        b3[cc][ks] = *reinterpret_cast<const bf16x8_t*>(w + FB_W3T + row * FL_HID + ks * 32 + 8 * (lane >> 4));
+    }
+    // biases of the lane's four output rows (C^T = Bt^T A^T: the weights are the A operand, so
+    // a lane receives four consecutive outputs of one event, eight over a pair of tiles,
+    // stored in one 16-byte write), read from LDS (registers held through the splines would
+    // spill): sampling starts the accumulators from them, the forward adds them after the
+    // products, as the training kernels do, so that these agree bit for bit.  (The forward
+    // with the activations as the A operand stored its outputs two bytes at a time:
+    // 33.3 against 32.2 us per layer of 2e5 events.)
+    for (int i = tid; i < FL_HID + FL_NOUTP; i += blockDim.x) {
+      const int c = (i - FL_HID) / 48, slot = (i - FL_HID) % 48;
+      bias_s[i] = i < FL_HID ? m[FO_B2 + i] : (slot < FL_NPAR ? m[FO_B3 + c * FL_NPAR + slot] : 0.f);
+    }
+    const H1Frag u1 = load_h1_frag(m, wave, lane);
+    const int xc = kFlowX[l][c], cc_in = kFlowC[l][c];
+    int64_t e0 = static_cast<int64_t>(blockIdx.x) * FL_TILE_F;
+    float cn = 0.5f, vn = 0.f;
+    if (e0 + e < B) {
+      cn = vin[(e0 + e) * FL_NDIM + cc_in];
+      vn = vin[(e0 + e) * FL_NDIM + xc];
+    }
+    for (; e0 < B; e0 += stride) {
+      const int64_t ev = e0 + e;
+      cond[e][c] = cn;
+      const float vx = vn;
+      if (ev + stride < B) {
+        cn = vin[(ev + stride) * FL_NDIM + cc_in];
+        vn = vin[(ev + stride) * FL_NDIM + xc];
+      }
+      __syncthreads();
+      // the three products run at a raised wave priority and the splines at the base one:
+      // a SIMD then issues the products of one block's waves ahead of another block's
+      // spline work, which keeps the co-resident blocks in different phases, the matrix
+      // cores busy beside the vector ALUs (measured 9 % faster than equal priorities, and
+      // 5 % faster than the reverse order)
+      __builtin_amdgcn_s_setprio(2);
+      mlp_h1(u1, cond, h1, FL_TILE_F);
+      __syncthreads();
+      // the lane's slots' biases are read once per layer and tile; ReLU and the bfloat16
+      // rounding on pairs (v_cvt_pk_bf16_f32, v_pk_max_i16)
       const f32x4_t bb2[2] = {*reinterpret_cast<const f32x4_t*>(bias_s + 32 * wave + 2 * kq),
                               *reinterpret_cast<const f32x4_t*>(bias_s + 32 * wave + 2 * kq + 4)};
 #pragma unroll
@@ -220,12 +223,13 @@ __global__ __launch_bounds__(256, 3) void k_flow_layer(const float* __restrict__
         f32x4_t acc[2];
 #pragma unroll
         for (int cc = 0; cc < 2; ++cc) {
-          acc[cc] = bb2[cc];
+          acc[cc] = SAMPLE ? bb2[cc] : zero;
 #pragma unroll
           for (int ks = 0; ks < FL_HID / 32; ++ks) {
             const bf16x8_t a = *reinterpret_cast<const bf16x8_t*>(h1 + (rb * 16 + ri) * FL_LDA + ks * 32 + kq8);
             acc[cc] = mfma_step(b2[cc][ks], a, acc[cc]);
           }
+          if (!SAMPLE) acc[cc] += bb2[cc];
         }
         *reinterpret_cast<uint4*>(h2 + (rb * 16 + ri) * FL_LDA + 32 * wave + 2 * kq) = pack_relu_bf16x8(acc[0], acc[1]);
       }
@@ -238,70 +242,35 @@ __global__ __launch_bounds__(256, 3) void k_flow_layer(const float* __restrict__
         f32x4_t acc[3];
 #pragma unroll
         for (int cc = 0; cc < 3; ++cc) {
-          acc[cc] = bb3[cc];
+          acc[cc] = SAMPLE ? bb3[cc] : zero;
 #pragma unroll
           for (int ks = 0; ks < FL_HID / 32; ++ks) {
             const bf16x8_t a = *reinterpret_cast<const bf16x8_t*>(h2 + (rb * 16 + ri) * FL_LDA + ks * 32 + kq8);
             acc[cc] = mfma_step(b3[cc][ks], a, acc[cc]);
           }
+          if (!SAMPLE) acc[cc] += bb3[cc];
         }
         _Float16* const q = par + (rb * 16 + ri) * FL_LDQ + wave * FL_SPS;
         *reinterpret_cast<uint4*>(q + 2 * kq) = make_uint4(pack_f16x2(acc[0][0], acc[0][1]), pack_f16x2(acc[0][2], acc[0][3]),
                                                            pack_f16x2(acc[1][0], acc[1][1]), pack_f16x2(acc[1][2], acc[1][3]));
         *reinterpret_cast<uint2*>(q + 32 + kq) = make_uint2(pack_f16x2(acc[2][0], acc[2][1]), pack_f16x2(acc[2][2], acc[2][3]));
       }
-    } else {
-      // the forward adds the bias after the products, as the backward's recomputation
-      // of the MLP does, so that the two agree bit for bit
-#pragma unroll
-      for (int rb = 0; rb < FL_TILE_F / 16; ++rb)
-#pragma unroll
-        for (int cc = 0; cc < 2; ++cc) {
-          f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int ks = 0; ks < FL_HID / 32; ++ks) {
-            const bf16x8_t a = *reinterpret_cast<const bf16x8_t*>(h1 + (rb * 16 + ri) * FL_LDA + ks * 32 + kq8);
-            acc = mfma_step(a, b2[cc][ks], acc);
-          }
-          const int col = (2 * wave + cc) * 16 + ri;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) h2[(rb * 16 + kq + j) * FL_LDA + col] = f2bf(fmaxf(acc[j] + bias2[cc], 0.f));
-        }
       __syncthreads();
-#pragma unroll
-      for (int rb = 0; rb < FL_TILE_F / 16; ++rb)
-#pragma unroll
-        for (int cc = 0; cc < 3; ++cc) {
-          f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int ks = 0; ks < FL_HID / 32; ++ks) {
-            const bf16x8_t a = *reinterpret_cast<const bf16x8_t*>(h2 + (rb * 16 + ri) * FL_LDA + ks * 32 + kq8);
-            acc = mfma_step(a, b3[cc][ks], acc);
-          }
-          const int col = (3 * wave + cc) * 16 + ri;  // parameter col % 47 of coordinate col / 47
-          if (col < FL_NOUT) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-              par[(rb * 16 + kq + j) * FL_LDQ + (col / FL_NPAR) * FL_SPS + col % FL_NPAR] =
-                  static_cast<_Float16>(acc[j] + bias3[cc]);
-          }
+      {
+        __builtin_amdgcn_s_setprio(0);
+        float ld = 0.f;
+        if (ev < B) {
+          const float o = spline_eval<SAMPLE>(par + e * FL_LDQ + c * FL_SPS, vx, ld);
+          vout[ev * FL_NDIM + xc] = o;
+          if (vout != vin) vout[ev * FL_NDIM + cc_in] = cond[e][c];
         }
-    }
-    __syncthreads();
-    {
-      __builtin_amdgcn_s_setprio(0);
-      float ld = 0.f;
-      if (ev < B) {
-        const float o = spline_eval<SAMPLE>(par + e * FL_LDQ + c * FL_SPS, vx, ld);
-        vout[ev * FL_NDIM + xc] = o;
-        if (vout != vin) vout[ev * FL_NDIM + cc_in] = cond[e][c];
+        // the event's four log s' (lanes 4e .. 4e+3): sums over lane pairs, then pairs of pairs
+        ld += quad_xor<0xB1>(ld);
+        ld += quad_xor<0x4E>(ld);
+        if (c == 0 && ev < B) logq[ev] = (s == 0 ? 0.f : logq[ev]) + ld;
       }
-      // the event's four log s' (lanes 4e .. 4e+3): sums over lane pairs, then pairs of pairs
-      ld += quad_xor<0xB1>(ld);
-      ld += quad_xor<0x4E>(ld);
-      if (c == 0 && ev < B) logq[ev] += ld;
+      __syncthreads();  // also: the tile's stores are seen by the block's next layer
     }
-    __syncthreads();
   }
 }
 
@@ -461,7 +430,7 @@ __device__ __forceinline__ int64_t batch_at(const BatchIdx& x, int64_t i) {
 // the six layers of 16 events per block (4 waves) in the density direction, and with BWD
 // the backward through them: activations stay in LDS (the spline parameters of all six
 // layers, binary16) and registers (the ReLU masks), so nothing is recomputed and a step has
-// no launch per layer.  Every value is formed by the operations of k_flow_layer<false> and
+// no launch per layer.  Every value is formed by the operations of k_flow_layers<false> and
 // k_flow_layer_bwd in their order: the same bits.
 //
 // Bound by latency: 16 events (the matrix instructions' tile) give a batch of 4096 one block
@@ -999,14 +968,13 @@ __global__ void k_flow_zero(float* p, int64_t n) {
 }
 
 // base points of a flow-proposal iteration: z_i = the event's Philox uniforms (binary32)
-__global__ void k_flow_zinit(uint64_t seed, uint32_t iter, int64_t n, float* z, float* logq) {
+__global__ void k_flow_zinit(uint64_t seed, uint32_t iter, int64_t n, float* z) {
   for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
        i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
     double u[FL_NDIM];
     event_uniforms<FL_NDIM>(seed, iter, static_cast<uint64_t>(i), FL_NDIM, u);
 #pragma unroll
     for (int d = 0; d < FL_NDIM; ++d) z[i * FL_NDIM + d] = static_cast<float>(u[d]);
-    logq[i] = 0.f;
   }
 }
 
@@ -1028,7 +996,7 @@ struct vegas_flow_state {
   void* mem;
   float *master, *grad, *m1, *m2;
   uint16_t* wb;
-  float *V;     // [7][max_batch][8] activations of the density direction
+  float *V;     // [6][max_batch][8] outputs of the layers of the density direction
   float *G;     // [2][max_batch][8] gradients w.r.t. layer outputs / inputs
   float *logq;  // [max_batch]
   float *glq;   // [max_batch]
@@ -1074,17 +1042,11 @@ int64_t grid_for(int64_t n, int per_block, int cap) {
   return g < 1 ? 1 : g;
 }
 
-// density direction over B events of y: V[0] = y, V[l+1] = layer l (V[l]); logq
-int flow_forward(vegas_flow_state* f, const float* y, int64_t B) {
-  VF_HIP(hipMemcpyAsync(f->V, y, sizeof(float) * FL_NDIM * B, hipMemcpyDeviceToDevice, f->stream));
-  hipLaunchKernelGGL(k_flow_zero, dim3(grid_for(B, 256, 1024)), dim3(256), 0, f->stream, f->logq, B);
+// density direction over B events of y: layer l's output in V + l vstride; logq
+int flow_forward(vegas_flow_state* f, const float* y, int64_t B, int64_t vstride, float* logq) {
+  hipLaunchKernelGGL(k_flow_layers<false>, dim3(grid_for(B, FL_TILE_F, kFwdBlocks)), dim3(256), 0, f->stream, f->master,
+                     f->wb, y, f->V, vstride, logq, B);
   VF_HIP(hipGetLastError());
-  const int64_t stride = static_cast<int64_t>(f->max_batch) * FL_NDIM;
-  for (int l = 0; l < FL_NLAYER; ++l) {
-    hipLaunchKernelGGL(k_flow_layer<false>, dim3(grid_for(B, FL_TILE_F, kFwdBlocks)), dim3(256), 0, f->stream, f->master,
-                       f->wb, l, f->V + l * stride, f->V + (l + 1) * stride, f->logq, B);
-    VF_HIP(hipGetLastError());
-  }
   return VEGAS_OK;
 }
 
@@ -1121,18 +1083,18 @@ int flow_gradient(vegas_flow_state* f, const float* y, const double* w, BatchIdx
       yb = f->yb;
       wbat = f->wbat;
     }
-    const int rc = flow_forward(f, yb, B);
+    const int64_t stride = static_cast<int64_t>(f->max_batch) * FL_NDIM;
+    const int rc = flow_forward(f, yb, B, stride, f->logq);
     if (rc != VEGAS_OK) return rc;
     hipLaunchKernelGGL(k_flow_seed, dim3(grid_for(B, 256, 1024)), dim3(256), 0, f->stream, wbat, B, f->glq, f->scal);
     VF_HIP(hipGetLastError());
-    const int64_t stride = static_cast<int64_t>(f->max_batch) * FL_NDIM;
     float* gout = f->G;           // dL/d z = 0 (uniform base density)
     float* gin = f->G + stride;
     hipLaunchKernelGGL(k_flow_zero, dim3(grid_for(B * FL_NDIM, 256, 1024)), dim3(256), 0, f->stream, gout, B * FL_NDIM);
     VF_HIP(hipGetLastError());
     for (int l = FL_NLAYER - 1; l >= 0; --l) {
       hipLaunchKernelGGL(k_flow_layer_bwd, dim3(grid_for(B, FL_TILE, 4096)), dim3(256), 0, f->stream, f->master, f->wb,
-                         l, f->V + l * stride, gout, gin, f->glq, B, bw);
+                         l, l == 0 ? yb : f->V + (l - 1) * stride, gout, gin, f->glq, B, bw);
       VF_HIP(hipGetLastError());
       launch_wgrad(1);
       VF_HIP(hipGetLastError());
@@ -1179,7 +1141,7 @@ int vegas_flow_create(int32_t max_batch, int64_t max_sample, uint64_t seed, void
   };
   const size_t o_master = take(4 * P), o_grad = take(4 * P), o_m1 = take(4 * P), o_m2 = take(4 * P);
   const size_t o_wb = take(2 * static_cast<size_t>(FB_LAYER) * FL_NLAYER);
-  const size_t o_V = take(4 * 7 * Bm * FL_NDIM), o_G = take(4 * 2 * Bm * FL_NDIM);
+  const size_t o_V = take(4 * 6 * Bm * FL_NDIM), o_G = take(4 * 2 * Bm * FL_NDIM);
   const size_t o_logq = take(4 * Bm), o_glq = take(4 * Bm), o_yb = take(4 * Bm * FL_NDIM), o_wbat = take(8 * Bm);
   const size_t o_scal = take(8 * 4);
   // the weight gradients' operands: six layers of a batch that runs in one launch, or one
@@ -1276,10 +1238,7 @@ int vegas_flow_density(vegas_flow f, const float* y_dev, int64_t B, float* logq_
     VF_HIP(hipGetLastError());
     return VEGAS_OK;
   }
-  const int rc = flow_forward(f, y_dev, B);
-  if (rc != VEGAS_OK) return rc;
-  VF_HIP(hipMemcpyAsync(logq_dev, f->logq, sizeof(float) * B, hipMemcpyDeviceToDevice, f->stream));
-  return VEGAS_OK;
+  return flow_forward(f, y_dev, B, 0, logq_dev);
 }
 
 int vegas_flow_loss_grad(vegas_flow f, const float* y_dev, const double* w_dev, int64_t B, float* grad_dev,
@@ -1335,14 +1294,9 @@ int vegas_flow_train_step(vegas_flow f, const float* y_dev, const double* w_dev,
 
 int vegas_flow_sample(vegas_flow f, const float* z_dev, int64_t n, float* y_dev, float* logq_dev) {
   if (!f || !z_dev || !y_dev || !logq_dev || n < 1) return VEGAS_EINVAL;
-  if (y_dev != z_dev) VF_HIP(hipMemcpyAsync(y_dev, z_dev, sizeof(float) * FL_NDIM * n, hipMemcpyDeviceToDevice, f->stream));
-  hipLaunchKernelGGL(k_flow_zero, dim3(grid_for(n, 256, 1024)), dim3(256), 0, f->stream, logq_dev, n);
+  hipLaunchKernelGGL(k_flow_layers<true>, dim3(grid_for(n, FL_TILE_F, kFwdBlocks)), dim3(256), 0, f->stream, f->master,
+                     f->wb, z_dev, y_dev, int64_t{0}, logq_dev, n);
   VF_HIP(hipGetLastError());
-  for (int l = FL_NLAYER - 1; l >= 0; --l) {
-    hipLaunchKernelGGL(k_flow_layer<true>, dim3(grid_for(n, FL_TILE_F, kFwdBlocks)), dim3(256), 0, f->stream, f->master,
-                       f->wb, l, y_dev, y_dev, logq_dev, n);
-    VF_HIP(hipGetLastError());
-  }
   return VEGAS_OK;
 }
 
@@ -1360,13 +1314,11 @@ int flow_sample_events(vegas_flow f, hipStream_t s, uint64_t seed, uint32_t iter
     VF_HIP(hipEventRecord(f->ev_ready, f->stream));
     VF_HIP(hipStreamWaitEvent(s, f->ev_ready, 0));
   }
-  hipLaunchKernelGGL(k_flow_zinit, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, seed, iter, n, f->zs, f->lqs);
+  hipLaunchKernelGGL(k_flow_zinit, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, seed, iter, n, f->zs);
   VF_HIP(hipGetLastError());
-  for (int l = FL_NLAYER - 1; l >= 0; --l) {
-    hipLaunchKernelGGL(k_flow_layer<true>, dim3(grid_for(n, FL_TILE_F, kFwdBlocks)), dim3(256), 0, s, f->master, f->wb, l,
-                       f->zs, f->zs, f->lqs, n);
-    VF_HIP(hipGetLastError());
-  }
+  hipLaunchKernelGGL(k_flow_layers<true>, dim3(grid_for(n, FL_TILE_F, kFwdBlocks)), dim3(256), 0, s, f->master, f->wb, f->zs,
+                     f->zs, int64_t{0}, f->lqs, n);
+  VF_HIP(hipGetLastError());
   *y = f->zs;
   *lq = f->lqs;
   return VEGAS_OK;

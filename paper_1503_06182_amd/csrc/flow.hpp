@@ -12,14 +12,13 @@
 // The forward kernels give each block (256 threads = 4 waves) tiles of 64
 // events: the first layer of the MLP on v_mfma_f32_16x16x4_f32 (K = 4), the two
 // 128-wide contractions on v_mfma_f32_16x16x32_bf16 (activations from LDS, the
-// layer's weights held in each wave's registers for the whole launch; the density
-// direction takes the activations as the A operand, the sampling direction the
-// weights), the spline parameters rounded to binary16 in LDS, then one thread per
-// (event, transformed coordinate) for the spline.  The backward kernel recomputes
-// the density direction's MLP (tiles of 32, weights from global memory, the same
-// MFMA sequence, so the same bits).  A spline is evaluated from its bin alone, which is
+// layer's weights, the A operand, held in each wave's registers), the spline parameters
+// rounded to binary16 in LDS, then one thread per (event, transformed coordinate) for the
+// spline; a block takes its tiles through all six layers.  The backward kernel recomputes
+// the density direction's MLP (tiles of 32, weights from global memory, operands
+// exchanged, the same sums, so the same bits).  A spline is evaluated from its bin alone, which is
 // found by bisection: a sampling layer of 2e5 events takes 119.5 us where forming all
-// 15 inner knots took 123, a density layer 33.3 where it took 34.
+// 15 inner knots took 123, a density layer of 2e5 events 33.3 where it took 34.
 #pragma once
 #include <hip/hip_bf16.h>
 #include <hip/hip_runtime.h>
