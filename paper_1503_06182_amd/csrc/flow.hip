@@ -113,15 +113,15 @@ __device__ __forceinline__ float quad_xor(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, false));
 }
 
-// the six coupling layers over a batch; SAMPLE: inverse splines (z -> y, layers 5 .. 0), else
+// coupling layers s0 .. s1 - 1 of six over a batch; SAMPLE: inverse splines (z -> y, layers 5 .. 0), else
 // forward (y -> z, layers 0 .. 5).  Step s reads what step s - 1 wrote (the first reads
 // vfirst) and writes vbuf + s vstride, in place when vstride is 0; vfirst may be vbuf.
 // logq[i] = sum of log s' of the transformed coordinates.  Tiles of 64 events; each wave
 // keeps the weight fragments of its output units (W2: 2 blocks of 16, W3: 3) for all eight
 // k-steps in registers for a layer.
 //
-// An event's layers need no other event, so a block takes its own tiles through all six and
-// no launch separates them: the blocks drift apart, and the last tiles of a layer (4.07 per
+// An event's layers need no other event, so a block can take its own tiles through all six
+// with no launch between them: the blocks drift apart, and the last tiles of a layer (4.07 per
 // block at 2e5 events) run beside the next layer's first.  A launch per layer cost 10 us
 // beyond the tiles' time, six times, and the caller's copies and fills: log q of 2e5 points
 // 200 -> 170 us, an iteration of 1e6 sampled events 701 -> 661.  (Loop-invariant addresses
@@ -129,7 +129,8 @@ __device__ __forceinline__ float quad_xor(float x) {
 template <bool SAMPLE>
 __global__ __launch_bounds__(256, 3) void k_flow_layers(const float* __restrict__ master,
                                                          const uint16_t* __restrict__ wb, const float* vfirst,
-                                                         float* vbuf, int64_t vstride, float* logq, int64_t B) {
+                                                         float* vbuf, int64_t vstride, float* logq, int64_t B,
+                                                         int s0, int s1) {
   // h1 is dead once the second layer has run (a barrier follows it), so the spline
   // parameters the third layer writes share its space: 52 KB per block, 3 blocks per CU
   static_assert(FL_TILE_F * FL_LDQ * sizeof(_Float16) >= FL_TILE_F * FL_LDA * sizeof(uint16_t), "h1 / par union");
@@ -149,7 +150,7 @@ __global__ __launch_bounds__(256, 3) void k_flow_layers(const float* __restrict_
   const int e = tid >> 2, c = tid & 3;
   const int64_t stride = static_cast<int64_t>(gridDim.x) * FL_TILE_F;
 #pragma unroll 1
-  for (int s = 0; s < FL_NLAYER; ++s) {
+  for (int s = s0; s < s1; ++s) {
     const int l = SAMPLE ? FL_NLAYER - 1 - s : s;
     const float* vin = s == 0 ? vfirst : vbuf + (s - 1) * vstride;
     float* vout = vbuf + s * vstride;
@@ -1042,11 +1043,21 @@ int64_t grid_for(int64_t n, int per_block, int cap) {
   return g < 1 ? 1 : g;
 }
 
-// density direction over B events of y: layer l's output in V + l vstride; logq
-int flow_forward(vegas_flow_state* f, const float* y, int64_t B, int64_t vstride, float* logq) {
-  hipLaunchKernelGGL(k_flow_layers<false>, dim3(grid_for(B, FL_TILE_F, kFwdBlocks)), dim3(256), 0, f->stream, f->master,
-                     f->wb, y, f->V, vstride, logq, B);
-  VF_HIP(hipGetLastError());
+// the layers over B events, vfirst -> vbuf (k_flow_layers), in one launch or one by one.
+// One launch saves the launches' fixed cost, which fades with the batch, and loses at the
+// largest ones, where blocks in different layers are slower than blocks in step (sampling
+// through a trained-like proposal, one launch against six: 2e5 events 182 and 209 us, 1e6 611
+// and 653, 3e6 1728 and 1770, 4e6 2317 and 2318, 6e6 3652 and 3440, 1e7 6260 and 5800)
+constexpr int64_t kOneLaunch = 3000000;
+template <bool SAMPLE>
+int flow_layers(vegas_flow_state* f, hipStream_t st, const float* vfirst, float* vbuf, int64_t vstride, float* logq,
+                int64_t B) {
+  const int step = B <= kOneLaunch ? FL_NLAYER : 1;
+  for (int s = 0; s < FL_NLAYER; s += step) {
+    hipLaunchKernelGGL(k_flow_layers<SAMPLE>, dim3(grid_for(B, FL_TILE_F, kFwdBlocks)), dim3(256), 0, st, f->master, f->wb,
+                       vfirst, vbuf, vstride, logq, B, s, s + step);
+    VF_HIP(hipGetLastError());
+  }
   return VEGAS_OK;
 }
 
@@ -1084,7 +1095,7 @@ int flow_gradient(vegas_flow_state* f, const float* y, const double* w, BatchIdx
       wbat = f->wbat;
     }
     const int64_t stride = static_cast<int64_t>(f->max_batch) * FL_NDIM;
-    const int rc = flow_forward(f, yb, B, stride, f->logq);
+    const int rc = flow_layers<false>(f, f->stream, yb, f->V, stride, f->logq, B);
     if (rc != VEGAS_OK) return rc;
     hipLaunchKernelGGL(k_flow_seed, dim3(grid_for(B, 256, 1024)), dim3(256), 0, f->stream, wbat, B, f->glq, f->scal);
     VF_HIP(hipGetLastError());
@@ -1238,7 +1249,7 @@ int vegas_flow_density(vegas_flow f, const float* y_dev, int64_t B, float* logq_
     VF_HIP(hipGetLastError());
     return VEGAS_OK;
   }
-  return flow_forward(f, y_dev, B, 0, logq_dev);
+  return flow_layers<false>(f, f->stream, y_dev, f->V, 0, logq_dev, B);
 }
 
 int vegas_flow_loss_grad(vegas_flow f, const float* y_dev, const double* w_dev, int64_t B, float* grad_dev,
@@ -1294,10 +1305,7 @@ int vegas_flow_train_step(vegas_flow f, const float* y_dev, const double* w_dev,
 
 int vegas_flow_sample(vegas_flow f, const float* z_dev, int64_t n, float* y_dev, float* logq_dev) {
   if (!f || !z_dev || !y_dev || !logq_dev || n < 1) return VEGAS_EINVAL;
-  hipLaunchKernelGGL(k_flow_layers<true>, dim3(grid_for(n, FL_TILE_F, kFwdBlocks)), dim3(256), 0, f->stream, f->master,
-                     f->wb, z_dev, y_dev, int64_t{0}, logq_dev, n);
-  VF_HIP(hipGetLastError());
-  return VEGAS_OK;
+  return flow_layers<true>(f, f->stream, z_dev, y_dev, 0, logq_dev, n);
 }
 
 }  // extern "C"
@@ -1316,9 +1324,8 @@ int flow_sample_events(vegas_flow f, hipStream_t s, uint64_t seed, uint32_t iter
   }
   hipLaunchKernelGGL(k_flow_zinit, dim3(grid_for(n, 256, 4096)), dim3(256), 0, s, seed, iter, n, f->zs);
   VF_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_flow_layers<true>, dim3(grid_for(n, FL_TILE_F, kFwdBlocks)), dim3(256), 0, s, f->master, f->wb, f->zs,
-                     f->zs, int64_t{0}, f->lqs, n);
-  VF_HIP(hipGetLastError());
+  const int rc = flow_layers<true>(f, s, f->zs, f->zs, 0, f->lqs, n);
+  if (rc != VEGAS_OK) return rc;
   *y = f->zs;
   *lq = f->lqs;
   return VEGAS_OK;

@@ -1,4 +1,4 @@
-"""The six coupling layers of a batch in one launch: a block takes its tiles of 64 events
+"""The six coupling layers of a batch in one launch (up to 3e6 events): a block takes its tiles of 64 events
 through all layers.  Events do not depend on each other, so every event's values equal, bit
 for bit, those of a batch that gives each block one tile (or the small batches' kernel) --
 at batch sizes where a block has one tile, one and a part, several, and in place."""
@@ -33,3 +33,15 @@ def test_density_and_sampling_by_parts(env, n):
     parts = [f.sample(y[i:i + 20_000].contiguous()) for i in range(0, n, 20_000)]
     assert torch.equal(x, torch.cat([p[0] for p in parts])) and torch.equal(sl, torch.cat([p[1] for p in parts]))
     assert torch.equal(f.density(y), lq)
+
+
+@pytest.mark.parametrize("n", [3_000_000, 3_000_001])
+def test_sampling_on_both_sides_of_the_launch_rule(env, n):
+    P, torch = env
+    f = P.Flow(max_batch=1)
+    f.set_params(random_theta(torch, 9))
+    z = points(torch, n, 6).cuda()
+    x, lq = f.sample(z)
+    for i in (0, 1_234_567, n - 30_000):
+        xp, lp = f.sample(z[i:i + 30_000].contiguous())
+        assert torch.equal(x[i:i + 30_000], xp) and torch.equal(lq[i:i + 30_000], lp), i
