@@ -54,11 +54,11 @@ sys.path.insert(0, ROOT)
 EVENT_KERNEL_WORK = {
     ("w_plus", "fp64"): {"algorithmic_f64": 341.5, "f64": 237.0, "f32": 0.0, "traffic": 15_524_147,
                          "events": 1_000_000},
-    ("ww_4l", "fp64"): {"algorithmic_f64": 813.0, "f64": 606.0, "f32": 0.0, "traffic": 166_888_141,
+    ("ww_4l", "fp64"): {"algorithmic_f64": 813.0, "f64": 606.0, "f32": 0.0, "traffic": 166_888_550,
                         "events": 10_000_000},
     ("ww_4l", "fp32me"): {"algorithmic_f64": None, "f64": 587.0, "f32": 419.0, "traffic": None,
                           "events": 10_000_000},
-    ("ww_had", "fp64"): {"algorithmic_f64": 1110.0, "f64": 874.0, "f32": 0.0, "traffic": 224_921_805,
+    ("ww_had", "fp64"): {"algorithmic_f64": 1110.0, "f64": 874.0, "f32": 0.0, "traffic": 224_920_986,
                          "events": 10_000_000},
 }
 # FP64 FLOPs of one call of the library's version of each mathematical function the
