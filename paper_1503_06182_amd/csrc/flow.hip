@@ -438,7 +438,7 @@ __device__ __forceinline__ int64_t batch_at(const BatchIdx& x, int64_t i) {
 // per CU; a layer's splines run on one wave while the others store the weight gradients'
 // operands, and each phase's weights are loaded before the spline or product that precedes
 // it.  4096 events: 68 us for the twelve launches' 195 (and the copies, fills and gaps between
-// them); a step of 32 launches took 366 us, its four launches take 116.
+// them); a step of 32 launches took 366 us, its four launches take 112.
 // ---------------------------------------------------------------------------
 constexpr int kEvTile = 16;
 constexpr int kWgSplit = 256;  // events per split of the weight gradients (more above kFusedBatch)
