@@ -257,6 +257,35 @@ __host__ __device__ __forceinline__ double fx2_value(long long D0, long long D1,
 }
 
 // ---------------------------------------------------------------------------
+// the same integers summed in digits of 48 bits (the event kernel's own fold).  A carry
+// leaves each column but the top one in [0, 2^48); kFoldEvents more digits of at most
+// 2^48 - 1 then stay inside 63 bits together with that remainder.  (With 2^15 events they
+// pass it by up to 2^48 - 2^15, and the arithmetic shifts below would carry a negative
+// amount: one observable bin of 65,536 events with a constant weight lost 1.2e-9 of its sum.)
+// ---------------------------------------------------------------------------
+constexpr unsigned long long kMask48 = 0xffffffffffffull, kMask32 = 0xffffffffull;
+constexpr uint32_t kFoldEvents = 511 * 64;  // events of a block between two carries
+static_assert(kFoldEvents * kMask48 + kMask48 + kFoldEvents <= 0x7fffffffffffffffull,
+              "digits, remainder and the carry from below must not leave 63 bits");
+
+// digits of 48 bits -> the 32-bit ones of a row (arithmetic shifts: low and high may be
+// negative sums)
+__device__ __forceinline__ void fold_row3(long long lo, long long hi, long long* r, int64_t stride) {
+  r[0] = lo & kMask32;
+  r[stride] = (lo >> 32) + ((hi & 0xffff) << 16);
+  r[2 * stride] = hi >> 16;
+}
+
+// carries of the block's histogram columns into the digits above (call with the whole
+// block, between barriers); stride: between the digits of one slot
+__device__ __forceinline__ void fold_carry(long long* c, int stride) {
+  const long long lo = c[0], mid = c[stride] + (lo >> 48);
+  c[0] = lo & kMask48;
+  c[stride] = mid & kMask48;
+  c[2 * stride] += mid >> 48;
+}
+
+// ---------------------------------------------------------------------------
 // wave64 reductions by DPP (row shifts 1, 2, 4, 8 within each row of 16 lanes, then
 // row 0 into row 1 and row 2 into row 3, then rows 0-1 into rows 2-3): the moves stay in
 // the VALU, where a butterfly's cross-lane permutes go through the LDS unit and wait

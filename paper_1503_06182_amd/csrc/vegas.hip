@@ -265,17 +265,16 @@ __device__ __forceinline__ void acc_sums_to_lds(LaneSums& ls, long long* acc) {
 // 48-bit digits: S1, S2 in the seven 32-bit-digit columns of the partial row, then per
 // grid slot {low, mid, top} (digit-major, like the row's columns) and per observable bin
 // {w low, w high, w top, w^2 low, w^2 mid, w^2 top}.  Between two carries a block adds at
-// most kFoldEvents events, so no column leaves 64 bits; the row is written in 32-bit
-// digits, and its value is the same integer whichever digits it is split into.
+// most kFoldEvents events (device_common.hpp), so no column leaves 64 bits; the row is written
+// in 32-bit digits, and its value is the same integer whichever digits it is split into.
 //
 // Bound by the VALU (the digits) and the LDS (random bins): against three or four 32-bit
 // digits, 5 x 1e7 W+W- events 1515 -> 1491 us, 3 x 3e6 hadronic 588 -> 576 (there also a
 // third wave per SIMD, which the smaller LDS allows), 5 x 9e5 stratified W+ 363 -> 351.
 // ---------------------------------------------------------------------------
-constexpr uint32_t kFoldEvents = 32768;      // events of a block between two carries
+static_assert(kFoldEvents % kWave == 0, "whole chunks between two carries");
 constexpr int kLds2 = 3;                     // LDS digits of a grid slot's w^2
 constexpr int kLdsObs = 6;                   // LDS digits of an observable bin
-constexpr unsigned long long kMask48 = 0xffffffffffffull, kMask32 = 0xffffffffull;
 __host__ __device__ constexpr int fold_cols(int nslot) { return kColHist + kLds2 * nslot; }
 __host__ __device__ constexpr int fold_obs_cols(int nobs) { return nobs > 0 ? kLdsObs * (nobs + 2) : 0; }
 
@@ -337,14 +336,6 @@ __device__ __forceinline__ void fold_obs(long long* acc, int col, const FoldDigi
   fold_hist(acc, col + 3, 1, g);
 }
 
-// digits of 48 bits -> the 32-bit ones of a row (arithmetic shifts: low and high may be
-// negative sums)
-__device__ __forceinline__ void fold_row3(long long lo, long long hi, long long* r, int64_t stride) {
-  r[0] = lo & kMask32;
-  r[stride] = (lo >> 32) + ((hi & 0xffff) << 16);
-  r[2 * stride] = hi >> 16;
-}
-
 // a block's per-lane sums, [total][lane] in LDS: the waves add theirs lane by lane, then one
 // wave per total sums its 64 slots.  (Each wave summing its own lanes, five sums of six
 // dependent 64-bit steps in every wave, took 2.3 us at the end of a 16-wave block.)
@@ -378,15 +369,6 @@ __device__ __forceinline__ void fold_sums_to_lds(BlockSums& red, long long* acc)
     red.v[k][lane] = 0;
     if (lane == 0) fold_total(k, t, acc);
   }
-}
-
-// carries of the block's histogram columns into the digits above (call with the whole
-// block, between barriers); stride: between the digits of one slot
-__device__ __forceinline__ void fold_carry(long long* c, int stride) {
-  const long long lo = c[0], mid = c[stride] + (lo >> 48);
-  c[0] = lo & kMask48;
-  c[stride] = mid & kMask48;
-  c[2 * stride] += mid >> 48;
 }
 
 struct EventArgs {
