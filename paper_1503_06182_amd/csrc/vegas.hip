@@ -2111,12 +2111,19 @@ int mail_wait(vegas_state* h, const MailArgs& m) {
   return VEGAS_OK;
 }
 
+// launches a one-block kernel of a read-back and returns this launch's own status: an error
+// that an earlier call of the thread left behind must not fail a read
+template <typename... P>
+hipError_t launch_mail(void (*k)(P...), int threads, hipStream_t st, P... p) {
+  void* args[] = {&p...};
+  return hipLaunchKernel(reinterpret_cast<const void*>(k), dim3(1), dim3(threads), args, 0, st);
+}
+
 // n doubles of device memory to the host; waits for the stream
 int read_back(vegas_state* h, const double* src, int n, double* out) {
   const MailArgs m = mail_next(h);
   if (m.dst) {
-    hipLaunchKernelGGL(k_mail, dim3(1), dim3(n > kWave ? 512 : kWave), 0, h->stream, src, n, m);
-    VG_HIP(hipGetLastError());
+    VG_HIP(launch_mail(k_mail, n > kWave ? 512 : kWave, h->stream, src, n, m));
     const int rc = mail_wait(h, m);
     if (rc == VEGAS_OK) std::memcpy(out, m.dst, sizeof(double) * n);
     return rc;
@@ -3262,9 +3269,8 @@ int vegas_set_state(vegas_handle h, const void* buf, size_t bytes) {
   if (m.dst) {
     std::memcpy(m.dst, e, sizeof(double) * (ne + nh));
     std::memcpy(m.dst + ne + nh, hd.fxs, sizeof(hd.fxs));
-    hipLaunchKernelGGL(k_unmail, dim3(1), dim3(512), 0, h->stream, m, h->b.edges, static_cast<int>(ne), h->b.history,
-                       static_cast<int>(nh), h->b.fxs);
-    VG_HIP(hipGetLastError());
+    VG_HIP(launch_mail(k_unmail, 512, h->stream, m, h->b.edges, static_cast<int>(ne), h->b.history,
+                       static_cast<int>(nh), h->b.fxs));
     const int rc = mail_wait(h, m);
     if (rc != VEGAS_OK) return rc;
   } else {
