@@ -1030,8 +1030,11 @@ int flow_prep(vegas_flow_state* f) {
   return VEGAS_OK;
 }
 
-// densities of up to this many events run their six layers in one launch
-constexpr int64_t kFusedDensity = 16384;
+// densities of up to this many points take k_flow_events (16 points per block) instead of
+// k_flow_layers (64 per block): two of its blocks per CU.  Its time grows by the round of 256
+// blocks, 4096 points 21.7 us, 8192 33.2, 12288 48.5, 16384 64.5, where the layers, a tile or
+// less for each CU, take 40.4 to 41.0 throughout (and the six launches of before took 50)
+constexpr int64_t kFusedDensity = 2 * 256 * kEvTile;
 
 // forward-kernel blocks: three resident per CU (LDS 44 KB, at most 168 VGPRs); more tiles
 // per block amortise the per-launch load of the weights into registers
