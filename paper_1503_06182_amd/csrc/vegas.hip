@@ -401,10 +401,13 @@ constexpr double kExtLo = 0x1p-40, kExtHi = 1.0 - 0x1p-40;
 // waves per SIMD that the register allocation must allow (W+W- with four spills 12 bytes a
 // lane: 1302 against 1311 us per 5 x 1e7 events, but 299 against 293 us for the small
 // iterations of the two-stage schedule; the hadronic W+W- with three spills 36 bytes and
-// took 573 us per 3 x 3e6 events when it got them, with two 581)
+// took 573 us per 3 x 3e6 events when it got them, with two 581; the Genz families, whose cos
+// and pow are the library's, spill 40 registers with four: family 1 in one dimension 19.7 against
+// 16.7 us at 1e5 events, 24.8 against 19.1 at 262,144, 65.5 against 49.0 at 4e6, in ten
+// dimensions 178 against 130, and at worst 56.6 against 60.8, family 4 in three dimensions)
 template <int PROC>
 constexpr int event_min_waves() {
-  return PROC == VEGAS_WW_HAD || PROC == VEGAS_WW_4L ? 3 : 4;
+  return PROC == VEGAS_WW_HAD || PROC == VEGAS_WW_4L || PROC == VEGAS_GENZ ? 3 : 4;
 }
 // threads of a block that fills a CU at that budget
 template <int PROC>
@@ -2305,9 +2308,15 @@ bool ext_supported(const vegas_state* h) {
 
 // threads of a full CU's event block
 int event_full(const vegas_state* h) {
-  static_assert(event_threads<VEGAS_WW_4L>() == event_threads<VEGAS_WW_HAD>());
-  const int p = h->cfg.process;
-  return p == VEGAS_WW_4L || p == VEGAS_WW_HAD ? event_threads<VEGAS_WW_4L>() : event_threads<VEGAS_W_PLUS>();
+  switch (h->cfg.process) {
+    case VEGAS_GENZ: return event_threads<VEGAS_GENZ>();
+    case VEGAS_WW_4L: return event_threads<VEGAS_WW_4L>();
+    case VEGAS_WW_HAD: return event_threads<VEGAS_WW_HAD>();
+    default: break;
+  }
+  static_assert(event_threads<VEGAS_GAUSS>() == 1024 && event_threads<VEGAS_EEMUMU>() == 1024 &&
+                event_threads<VEGAS_DY_Z>() == 1024 && event_threads<VEGAS_W_PLUS>() == 1024);
+  return 1024;
 }
 
 template <int PROC, int PREC, int D, bool FUSED, bool OBS>
