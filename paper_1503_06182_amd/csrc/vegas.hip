@@ -58,7 +58,7 @@ __host__ __device__ constexpr int hist_cols(int nslot) { return kColHist + kD2 *
 // number of 32-column (256-byte) tiles, so that every tile the column reduction reads
 // is aligned to the 128-byte lines it is fetched in
 __host__ __device__ constexpr int part_ld(int ncol) { return (ncol + 31) & ~31; }
-constexpr int kFusedLdsMax = 64 * 1024; // LDS of an event block (grid + digits) that allows the fused fold
+constexpr int kFusedLdsMax = 64 * 1024; // row digits + grid (+ lanes' sums) that allow the fused fold (configure_lds)
 // observable histogram: bins 1..nobs uniform on [lo, hi), 0 = underflow, nobs + 1 = overflow
 constexpr int kObsLd = VEGAS_MAX_OBS_BINS + 2;
 constexpr int kStrataBlocks = 1024;  // blocks of the hypercube fold (rows of its partials)
@@ -344,6 +344,8 @@ struct BlockSums {
   unsigned long long v[kFoldLane + 1][kWave];
 };
 
+constexpr size_t kEventStaticLds = sizeof(BlockSums) + 4 * sizeof(uint32_t);  // an event block's own
+
 // total k (a wave's share of 48-bit digits, weight 2^(48 (k mod 2)), the fifth 2^96 of w^2)
 // -> the S1, S2 columns, by lane 0: the two 32-bit digits it reaches
 __device__ __forceinline__ void fold_total(int k, long long t, long long* acc) {
@@ -415,6 +417,11 @@ constexpr int event_threads() {
   return 4 * kWave * event_min_waves<PROC>();
 }
 
+// 10 or more fixed dimensions (the hadronic W+W-): the register budget of three waves per SIMD
+// is spent on the integrand, so the lanes' digit sums live in LDS
+template <int D>
+constexpr bool kLaneSlots = D >= 10;
+
 // the kernel's arguments, read again by scalar loads where they are used: hoisted out of the
 // event loop, the integrand's constants took more scalar registers than there are and
 // were read back lane by lane on the VALU (W+W-: 36 of 872 instructions of a pass; the
@@ -469,10 +476,9 @@ __global__ __launch_bounds__(MAXT) void k_event(EventArgs a) {
   }
   if constexpr (FUSED)
     for (int i = threadIdx.x; i < fcol; i += blockDim.x) acc[i] = 0;
-  // with 10 or more dimensions the register budget of 2 waves per SIMD is spent on the
-  // integrand, so the lane's S1, S2 digit sums live in LDS, one private slot per lane
-  // and digit (no atomics: no other lane touches it) instead of 10 registers
-  constexpr bool kLdsSums = FUSED && D >= 10 && MAXT == event_threads<PROC>();
+  // the lane's S1, S2 digit sums in LDS instead of 10 registers (kLaneSlots), one private slot
+  // per lane and digit (no atomics: no other lane touches it)
+  constexpr bool kLdsSums = FUSED && kLaneSlots<D> && MAXT == event_threads<PROC>();
   long long* lsum = acc + fcol;  // kLdsSums: [kFoldLane][blockDim.x]
   const int lsn = static_cast<int>(blockDim.x);
   if constexpr (kLdsSums)
@@ -2047,7 +2053,8 @@ struct vegas_state {
   bool s_have_sig;              // s_sig holds the last stratified iteration's sigma_h
   int64_t last_strata_npc;      // last iteration: events per hypercube (equal counts), -1 adaptive,
                                 //   0 not stratified
-  size_t smem_max;              // LDS per block the launches may use
+  size_t smem_max;              // LDS per block of the folds and the finalisation
+  size_t lds_device;            // the device's limit per block (event blocks)
   int refine_lds;               // LDS of the refinement scratch: D * 4 (n + 1) doubles
   bool scale_valid;             // the device holds scales from a previous iteration (b.fxs)
   int ncu, occ_event, occ_event_fused;  // CUs, and resident blocks of a full CU's threads (event_full) per CU
@@ -2228,10 +2235,12 @@ void stage_collect(vegas_state* h) {
   h->ev_pending.clear();
 }
 
-// LDS of an event block: with 10 or more dimensions the lanes' sums as well
+// dynamic LDS of an event block of a kernel with compile-time dimension D (0: run-time, whose
+// lanes keep their sums in registers)
+template <int D>
 int event_block_lds(const vegas_state* h, bool fused, int threads) {
   if (!fused) return h->event_lds;
-  return h->fused_lds + (h->D >= 10 ? static_cast<int>(sizeof(long long)) * kFoldLane * threads : 0);
+  return h->fused_lds + (kLaneSlots<D> ? static_cast<int>(sizeof(long long)) * kFoldLane * threads : 0);
 }
 
 // two instantiations where a full CU's block (event_threads, the performance path) has
@@ -2242,7 +2251,7 @@ hipError_t launch_event_tfo(vegas_state* h, const EventArgs& a, int blocks, int 
   TimedLaunch t(h, 0);
   if (threads <= kFull)
     hipExtLaunchKernelGGL((k_event<PROC, PREC, D, kFull, EXT, FUSED, OBS, STRAT>), dim3(blocks), dim3(threads),
-                          event_block_lds(h, FUSED, threads), h->stream, t.e0, t.e1, 0, a);
+                          event_block_lds<D>(h, FUSED, threads), h->stream, t.e0, t.e1, 0, a);
   else if constexpr (!EXT && kFull < 1024)
     hipExtLaunchKernelGGL((k_event<PROC, PREC, D, 1024, false, FUSED, OBS, STRAT>), dim3(blocks), dim3(threads),
                           FUSED ? h->fused_lds : h->event_lds, h->stream, t.e0, t.e1, 0, a);
@@ -2326,7 +2335,9 @@ const void* event_kernel_ptr(bool strat) {
 }
 
 template <int PROC, int PREC, int D>
-int occupancy_event_t(int lds, bool fused, bool obs, bool strat) {
+int occupancy_event_t(const vegas_state* h, bool fused) {
+  const bool obs = h->nobs > 0, strat = h->strata_m > 0;
+  const int lds = event_block_lds<D>(h, fused, event_threads<PROC>());
   int nb = 0;
   const void* k = fused ? (obs ? event_kernel_ptr<PROC, PREC, D, true, true>(strat)
                                : event_kernel_ptr<PROC, PREC, D, true, false>(strat))
@@ -2338,20 +2349,18 @@ int occupancy_event_t(int lds, bool fused, bool obs, bool strat) {
 }
 
 int occupancy_event(const vegas_state* h, bool fused) {
-  const int lds = event_block_lds(h, fused, event_full(h));
-  const bool o = h->nobs > 0, st = h->strata_m > 0;
   switch (h->cfg.process) {
-    case VEGAS_GAUSS: return occupancy_event_t<VEGAS_GAUSS, VEGAS_FP64, 0>(lds, fused, o, st);
-    case VEGAS_GENZ: return occupancy_event_t<VEGAS_GENZ, VEGAS_FP64, 0>(lds, fused, o, st);
-    case VEGAS_EEMUMU: return occupancy_event_t<VEGAS_EEMUMU, VEGAS_FP64, 2>(lds, fused, o, st);
-    case VEGAS_DY_Z: return occupancy_event_t<VEGAS_DY_Z, VEGAS_FP64, 3>(lds, fused, o, st);
-    case VEGAS_W_PLUS: return occupancy_event_t<VEGAS_W_PLUS, VEGAS_FP64, 4>(lds, fused, o, st);
+    case VEGAS_GAUSS: return occupancy_event_t<VEGAS_GAUSS, VEGAS_FP64, 0>(h, fused);
+    case VEGAS_GENZ: return occupancy_event_t<VEGAS_GENZ, VEGAS_FP64, 0>(h, fused);
+    case VEGAS_EEMUMU: return occupancy_event_t<VEGAS_EEMUMU, VEGAS_FP64, 2>(h, fused);
+    case VEGAS_DY_Z: return occupancy_event_t<VEGAS_DY_Z, VEGAS_FP64, 3>(h, fused);
+    case VEGAS_W_PLUS: return occupancy_event_t<VEGAS_W_PLUS, VEGAS_FP64, 4>(h, fused);
     case VEGAS_WW_4L:
       if (h->cfg.precision == VEGAS_FP32_ME)
-        return occupancy_event_t<VEGAS_WW_4L, VEGAS_FP32_ME, 8>(lds, fused, o, st);
-      return occupancy_event_t<VEGAS_WW_4L, VEGAS_FP64, 8>(lds, fused, o, st);
+        return occupancy_event_t<VEGAS_WW_4L, VEGAS_FP32_ME, 8>(h, fused);
+      return occupancy_event_t<VEGAS_WW_4L, VEGAS_FP64, 8>(h, fused);
     case VEGAS_WW_HAD:
-      return occupancy_event_t<VEGAS_WW_HAD, VEGAS_FP64, 10>(lds, fused, o, st);
+      return occupancy_event_t<VEGAS_WW_HAD, VEGAS_FP64, 10>(h, fused);
   }
   return 1;
 }
@@ -2371,11 +2380,15 @@ void configure_lds(vegas_state* h) {
   h->acc_groups = (D + dpg - 1) / dpg;
   h->acc_lds = static_cast<int>(sizeof(long long) * (hist_cols(dpg * n) + ocol));
   const int full = static_cast<int>(sizeof(long long) * (hist_cols(D * n) + ocol));
-  // the fused fold is used where the finalisation can also re-fold in one block's LDS (the
-  // row's digits beside the grid); its own blocks hold 48-bit digits and, with 10 or more
-  // dimensions, the lanes' sums (event_block_lds)
-  h->fused_ok = h->event_lds + full + (D >= 10 ? static_cast<int>(sizeof(long long) * kLane * 256) : 0) <= kFusedLdsMax;
   h->fused_lds = h->event_lds + static_cast<int>(sizeof(long long) * (fold_cols(D * n) + fold_obs_cols(h->nobs)));
+  // the fused fold is used where the finalisation can also re-fold in one block's LDS: the
+  // row's digits, beside a grid and (10 or more dimensions) 256 lanes' sums, within kFusedLdsMax.
+  // Which fold an iteration takes shows in its last bits, so that line does not follow the event
+  // blocks, which hold fewer digits but more lanes; those have to fit the device's LDS besides
+  // (hadronic W+W- at most 75,448 bytes, the others at most 56,352, of 163,840)
+  const int row_rule = h->event_lds + full + (D >= 10 ? static_cast<int>(sizeof(long long) * kLane * 256) : 0);
+  const int block = h->cfg.process == VEGAS_WW_HAD ? event_block_lds<10>(h, true, event_full(h)) : h->fused_lds;
+  h->fused_ok = row_rule <= kFusedLdsMax && static_cast<size_t>(block) + kEventStaticLds <= h->lds_device;
   h->fin_lds = h->fused_ok ? full : 0;
   h->refine_lds = static_cast<int>(sizeof(double) * 4 * D * (n + 1));
   const int obs_lds = h->nobs ? static_cast<int>(sizeof(double) * 2 * (h->nobs + 2)) : 0;
@@ -2489,6 +2502,7 @@ int vegas_init(const vegas_config* cfg, int64_t max_events, void* workspace, siz
     if (h->ncu < 1) h->ncu = 1;
     size_t smem = have_prop ? prop.sharedMemPerBlock : 65536;
     h->smem_max = smem > 65536 ? 65536 : smem;
+    h->lds_device = smem;
     configure_lds(h);
   }
   // zero the device-wide atomics and every buffer after the partials; the uniform grid
