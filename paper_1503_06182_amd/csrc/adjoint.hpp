@@ -45,6 +45,11 @@ constexpr int kTreeRows = 256;
 // for 64 points x 1e6 events, and each wave pays the couplings of its point once per row.
 // A function of the number of events alone.
 constexpr int64_t kGradRows = 4096;
+// A lane's sums are set aside every kGradStretch events of the lane, so that the chains of
+// additions do not grow with the row: at most kGradStretch events, then one addition per
+// stretch (2048 of them at the largest call, 2^31 - 1 events and 64 points, where a row has
+// 8192 tiles and a lane would add 524,288 events one by one; 1e8 events 10.35 ms either way)
+constexpr int kGradStretch = 256;
 inline int64_t grad_tiles_per_row(int64_t ntiles) { return (ntiles + kGradRows - 1) / kGradRows; }
 
 struct GradArgs {
@@ -130,7 +135,7 @@ __global__ __launch_bounds__(256, 4) void k_dy_grad(GradArgs a) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int wpb = blockDim.x >> 6;
   double* ev = sm + 3 * (n + 1) + wave * kGradLds;       // [65][4]
-  double* gs = ev + 65 * 4;                              // [8][64]
+  double* gs = ev + 65 * 4;                              // [8][64]: stretches, then groups
   for (int i = threadIdx.x; i < 3 * (n + 1); i += blockDim.x) e_lds[i] = a.edges[i];
   if (lane < 4) ev[64 * 4 + lane] = lane == 1 ? -1.0 : 0.0;
 
@@ -173,7 +178,19 @@ __global__ __launch_bounds__(256, 4) void k_dy_grad(GradArgs a) {
        row += static_cast<int64_t>(gridDim.x) * wpb) {
     const int64_t t1 = min(a.ntiles, (row + 1) * a.tiles_per_row);
     double S[kGradSums] = {0, 0, 0, 0, 0, 0, 0, 0};
+    bool aside = false;  // gs holds the sums of the stretches before
+    int left = kGradStretch / 64 * G;  // tiles, of ceil(64 / G) events per lane each
     for (int64_t tile = row * a.tiles_per_row; tile < t1; ++tile) {
+      if (--left < 0) {
+#pragma unroll
+        for (int k = 0; k < kGradSums; ++k) {
+          double* const q = gs + k * 64 + lane;
+          *q = aside ? *q + S[k] : S[k];
+          S[k] = 0.0;
+        }
+        aside = true;
+        left += kGradStretch / 64 * G;
+      }
       // wave priorities: phase 1 (uniforms, grid map, kinematics) at the base priority,
       // phase 2 (the parameter points' sums) raised, so that the waves of a SIMD drift
       // apart in phase
@@ -236,6 +253,9 @@ __global__ __launch_bounds__(256, 4) void k_dy_grad(GradArgs a) {
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
+    if (aside)
+#pragma unroll
+      for (int k = 0; k < kGradSums; ++k) S[k] += gs[k * 64 + lane];
     // the groups' sums in group order
     if (G > 1) {
 #pragma unroll
