@@ -73,21 +73,21 @@ __device__ __forceinline__ double fma_coef(double a, double b, double c) {
   return d;
 }
 
-// exp(t) for |t| up to about 1e9 (0 and inf where it leaves the range): t = k ln 2 + r, ln 2
-// in two parts, exp(r) = 1 + r + r^2 q(r) with q the degree-9 interpolation at Chebyshev
-// nodes of |r| <= ln(2)/2 (1.6e-17 relative), then the exponent.  No branches; NaN stays NaN
+// exp(t) for |t| up to about 1e9 (0 and inf where it leaves the range), exp_fin's polynomial in
+// the form that suits this loop (k rounded and converted, the additions by fma_coef).  No
+// branches; NaN stays NaN
 __device__ __forceinline__ double exp_core(double t) {
   const double k = rint(t * 1.4426950408889634);
-  const double r = __fma_rn(-k, 2.3190468138462996e-17, __fma_rn(-k, 0.6931471805599453, t));
-  double q = fma_coef(2.510038549551032e-08, r, 2.7620088445409746e-07);
-  q = fma_coef(q, r, 2.7557268459997064e-06);
-  q = fma_coef(q, r, 2.4801521295954376e-05);
-  q = fma_coef(q, r, 0.00019841269863053618);
-  q = fma_coef(q, r, 0.0013888888917213717);
-  q = fma_coef(q, r, 0.008333333333330062);
-  q = fma_coef(q, r, 0.04166666666662413);
-  q = fma_coef(q, r, 0.16666666666666669);
-  q = fma_coef(q, r, 0.5000000000000001);
+  const double r = __fma_rn(-k, kLn2Lo, __fma_rn(-k, kLn2, t));
+  double q = fma_coef(kExpQ[9], r, kExpQ[8]);
+  q = fma_coef(q, r, kExpQ[7]);
+  q = fma_coef(q, r, kExpQ[6]);
+  q = fma_coef(q, r, kExpQ[5]);
+  q = fma_coef(q, r, kExpQ[4]);
+  q = fma_coef(q, r, kExpQ[3]);
+  q = fma_coef(q, r, kExpQ[2]);
+  q = fma_coef(q, r, kExpQ[1]);
+  q = fma_coef(q, r, kExpQ[0]);
   return ldexp(__fma_rn(r * r, q, r) + 1.0, static_cast<int>(k));
 }
 

@@ -193,6 +193,9 @@ __device__ __forceinline__ double log_pos(double x) {
 }
 
 // t = k ln 2 + r with |r| <= ln(2)/2; exp(r) - 1 = r + r^2 q(r), q of degree 9 (1.6e-17 of exp r)
+constexpr double kExpQ[10] = {0.5000000000000001,     0.16666666666666669,    0.04166666666662413,    0.008333333333330062,
+                              0.0013888888917213717,  0.00019841269863053618, 2.4801521295954376e-05, 2.7557268459997064e-06,
+                              2.7620088445409746e-07, 2.510038549551032e-08};
 __device__ __forceinline__ double exp_fold(double t, int& k, double& r) {
   constexpr double kRound = 0x1.8p52;  // a sum with it is rounded to an integer, its last bits
   const double kr = __fma_rn(t, 1.4426950408889634, kRound);
@@ -201,15 +204,15 @@ __device__ __forceinline__ double exp_fold(double t, int& k, double& r) {
   k = static_cast<int>(static_cast<uint32_t>(b));
   const double dk = kr - kRound;
   r = __fma_rn(-dk, kLn2Lo, __fma_rn(-dk, kLn2, t));
-  double q = __fma_rn(r, poly_coef(2.510038549551032e-08), poly_coef(2.7620088445409746e-07));
-  q = __fma_rn(q, r, poly_coef(2.7557268459997064e-06));
-  q = __fma_rn(q, r, poly_coef(2.4801521295954376e-05));
-  q = __fma_rn(q, r, poly_coef(0.00019841269863053618));
-  q = __fma_rn(q, r, poly_coef(0.0013888888917213717));
-  q = __fma_rn(q, r, poly_coef(0.008333333333330062));
-  q = __fma_rn(q, r, poly_coef(0.04166666666662413));
-  q = __fma_rn(q, r, poly_coef(0.16666666666666669));
-  return __fma_rn(q, r, poly_coef(0.5000000000000001));
+  double q = __fma_rn(r, poly_coef(kExpQ[9]), poly_coef(kExpQ[8]));
+  q = __fma_rn(q, r, poly_coef(kExpQ[7]));
+  q = __fma_rn(q, r, poly_coef(kExpQ[6]));
+  q = __fma_rn(q, r, poly_coef(kExpQ[5]));
+  q = __fma_rn(q, r, poly_coef(kExpQ[4]));
+  q = __fma_rn(q, r, poly_coef(kExpQ[3]));
+  q = __fma_rn(q, r, poly_coef(kExpQ[2]));
+  q = __fma_rn(q, r, poly_coef(kExpQ[1]));
+  return __fma_rn(q, r, poly_coef(kExpQ[0]));
 }
 
 // exp t and exp t - 1 for |t| < 1e9 (0 and inf, or -1 and inf, where they leave the range)
@@ -494,8 +497,7 @@ __device__ __forceinline__ cx<R> chain01(const cx<R> e2[4], const R k[4], R B00,
 }
 
 // exchange-propagator invariants: t = k^2 and k^0 -+ k^3 for k = p1 - q(W+) (u quark)
-// and k = p1 - q(W-) (d quark); given when they were formed in binary64 from the
-// mapped masses (used by the binary32 amplitude), else taken from the momenta
+// and k = p1 - q(W-) (d quark), formed in binary64 from the mapped masses
 template <typename R>
 struct ExchInv {
   R tu, td, b00u, b11u, b00d, b11d;
@@ -528,7 +530,7 @@ __device__ __forceinline__ void lepton_current(const double pa[4], const double 
 // polarisations ep, em up to those factors) and the W momenta qp, qm
 template <typename R>
 __device__ __forceinline__ R ww_me2(const PhysConst& c, const cx<R> ep[4], const cx<R> em[4], const R qp[4],
-                                    const R qm[4], const ExchInv<R>* inv) {
+                                    const R qm[4], const ExchInv<R>& inv) {
   R Ppq[4], Pmq[4], dq[4];
 #pragma unroll
   for (int mu = 0; mu < 4; ++mu) {
@@ -551,22 +553,7 @@ __device__ __forceinline__ R ww_me2(const PhysConst& c, const cx<R> ep[4], const
   const R half = rs * R(0.5);
   R ku[4] = {half - qp[0], -qp[1], -qp[2], half - qp[3]};
   R kd[4] = {half - qm[0], -qm[1], -qm[2], half - qm[3]};
-  R tu, td, b00u, b11u, b00d, b11d;
-  if (inv) {
-    tu = inv->tu;
-    td = inv->td;
-    b00u = inv->b00u;
-    b11u = inv->b11u;
-    b00d = inv->b00d;
-    b11d = inv->b11d;
-  } else {
-    tu = ku[0] * ku[0] - ku[1] * ku[1] - ku[2] * ku[2] - ku[3] * ku[3];
-    td = kd[0] * kd[0] - kd[1] * kd[1] - kd[2] * kd[2] - kd[3] * kd[3];
-    b00u = ku[0] - ku[3];
-    b11u = ku[0] + ku[3];
-    b00d = kd[0] - kd[3];
-    b11d = kd[0] + kd[3];
-  }
+  const R tu = inv.tu, td = inv.td, b00u = inv.b00u, b11u = inv.b11u, b00d = inv.b00d, b11d = inv.b11d;
   const cx<R> Tu = chain01(em, ku, b00u, b11u, ep);
   const cx<R> Td = chain01(ep, kd, b00d, b11d, em);
   const R ct = static_cast<R>(c.ct);
@@ -879,7 +866,7 @@ __device__ __forceinline__ double f_ww_single(const PhysConst& c, const double* 
   iv.b11u = static_cast<R>(rs - (Ep + q * ct));
   iv.b00d = static_cast<R>(-emm);
   iv.b11d = static_cast<R>(rs - (Em - q * ct));
-  const double me = static_cast<double>(ww_me2<R>(c, Jp, Jm, qpr, qmr, &iv));
+  const double me = static_cast<double>(ww_me2(c, Jp, Jm, qpr, qmr, iv));
   const double gbw = (c.gs * c.gs) * c.invMG, ish = 1.0 / sh;
   return (c.conv * kWWPS) * (gbw * gbw) * (ish * ish) * (sl * me) * (rho_rng * rrng2);
 }

@@ -204,13 +204,9 @@ struct EvDigits {
   long long d[kD1], h[kD2];
 };
 
-// S1, S2 digits of w; returns the digits of w and of w^2 for the histograms.
-// NONNEG: the process's weights are never negative (cross sections, the Gaussian), so the
-// digits of w need no sign handling
-template <bool NONNEG>
+// S1, S2 digits of w; returns the digits of w and of w^2 for the histograms
 __device__ __forceinline__ void acc_sums(double w, int E1, int E2, LaneSums& ls, EvDigits& g) {
-  if constexpr (NONNEG) fx_digits_pos(w, E1, g.d[0], g.d[1], g.d[2]);
-  else fx_digits(w, E1, g.d[0], g.d[1], g.d[2]);
+  fx_digits(w, E1, g.d[0], g.d[1], g.d[2]);
   fx2_digits(w * w, E2, g.h);  // w^2 of a finite weight: >= 0
 #pragma unroll
   for (int k = 0; k < kD1; ++k) ls.v[k] += g.d[k];
@@ -218,34 +214,26 @@ __device__ __forceinline__ void acc_sums(double w, int E1, int E2, LaneSums& ls,
   for (int k = 0; k < kD2; ++k) ls.v[kD1 + k] += g.h[k];
 }
 
-// the top digit of w^2 is zero unless this iteration's w^2 came within 2^-32 of the
-// scale (the scale sits 2^32 above the previous iteration's largest): the histogram
-// adds it only when some active lane of the wave has it (a wave-uniform test; adding
-// zero changes nothing, so the totals are the same either way)
-__device__ __forceinline__ bool top_digit_needed(const EvDigits& g) { return __ballot(g.h[3] != 0) != 0ull; }
-
-// the digits are added whether or not they are zero (but the top digit, see
-// top_digit_needed): a branch around each atomic cost more (2 % of the W+ and W+W- event
-// kernels) than the atomics it saved.  The LDS byte offset is formed in 32 bits
+// an LDS column; its byte offset is formed in 32 bits
 __device__ __forceinline__ unsigned long long* lds_col(long long* acc, int col) {
   return reinterpret_cast<unsigned long long*>(reinterpret_cast<char*>(acc) + static_cast<uint32_t>(col) * 8u);
 }
 
 // the digits of w^2 to columns col, col + stride, col + 2 stride, col + 3 stride
-__device__ __forceinline__ void acc_hist(long long* acc, int col, int stride, const EvDigits& g, bool top) {
+__device__ __forceinline__ void acc_hist(long long* acc, int col, int stride, const EvDigits& g) {
   unsigned long long* p = lds_col(acc, col);
   atomicAdd(p, static_cast<unsigned long long>(g.h[0]));
   atomicAdd(p + stride, static_cast<unsigned long long>(g.h[1]));
   atomicAdd(p + 2 * stride, static_cast<unsigned long long>(g.h[2]));
-  if (top) atomicAdd(p + 3 * stride, static_cast<unsigned long long>(g.h[3]));
+  atomicAdd(p + 3 * stride, static_cast<unsigned long long>(g.h[3]));
 }
 
 // observable bin (seven consecutive columns): the digits of w, then those of w^2
-__device__ __forceinline__ void acc_obs(long long* acc, int col, const EvDigits& g, bool top) {
+__device__ __forceinline__ void acc_obs(long long* acc, int col, const EvDigits& g) {
   unsigned long long* p = lds_col(acc, col);
 #pragma unroll
   for (int k = 0; k < kD1; ++k) atomicAdd(p + k, static_cast<unsigned long long>(g.d[k]));
-  acc_hist(acc, col + kD1, 1, g, top);
+  acc_hist(acc, col + kD1, 1, g);
 }
 
 // per-lane S1, S2 -> wave butterfly -> LDS columns 0 .. kLane - 1 (call with the whole block)
@@ -286,8 +274,12 @@ __device__ __forceinline__ long long int52(double v) {
 // a lane's sums between two carries: w in {low, high}, w^2 in {low, mid, top}
 constexpr int kFoldLane = 5;
 
-// the digits of one event: w = d[1] 2^48 + d[0], w^2 = h[2] 2^96 + h[1] 2^48 + h[0]; the
-// top digit is there only if some active lane of the wave has one (see top_digit_needed)
+// the digits of one event: w = d[1] 2^48 + d[0], w^2 = h[2] 2^96 + h[1] 2^48 + h[0].  The top
+// digit of w^2 is zero unless this iteration's w^2 came within 2^-30 of the scale (which
+// sits 2^32 above the previous iteration's largest): top tells whether some active lane of
+// the wave has one (a wave-uniform test; adding zero changes nothing, so the totals are the
+// same either way).  The other digits are added whether or not they are zero: a branch around
+// each atomic cost more than the atomics it saved
 struct FoldDigits {
   long long d[2], h[3];
   bool top;
@@ -1089,14 +1081,14 @@ __global__ void k_accum(AccArgs a) {
     const double w = a.b.rec_w[i];
     if (w == 0.0) continue;
     EvDigits g;
-    acc_sums<false>(w, E1, E2, ls, g);
+    acc_sums(w, E1, E2, ls, g);
     // the same digits of w^2 go to the event's bin in every dimension
     for (int d = dlo; d < dhi; ++d) {
       const uint32_t word = a.b.rec_bins[(d >> 2) * a.stride_rec + i];
       const int bin = static_cast<int>((word >> (8 * (d & 3))) & 0xffu);
-      acc_hist(acc, hist_col((d - dlo) * n + bin), lslots, g, true);
+      acc_hist(acc, hist_col((d - dlo) * n + bin), lslots, g);
     }
-    if (ocol) acc_obs(acc, lcol + kObsW * static_cast<int>(a.b.rec_obs[i]), g, true);
+    if (ocol) acc_obs(acc, lcol + kObsW * static_cast<int>(a.b.rec_obs[i]), g);
   }
   acc_sums_to_lds(ls, acc);
   __syncthreads();
@@ -1271,12 +1263,12 @@ __device__ __forceinline__ void finalize_block(const FinArgs& f, unsigned char* 
       const double w = b.rec_w[i];
       if (w == 0.0) continue;
       EvDigits g;
-      acc_sums<false>(w, E1, E2, ls, g);
+      acc_sums(w, E1, E2, ls, g);
       for (int d = 0; d < nd; ++d) {
         const uint32_t word = b.rec_bins[(d >> 2) * f.stride_rec + i];
-        acc_hist(acc, hist_col(d * n + static_cast<int>((word >> (8 * (d & 3))) & 0xffu)), nslot, g, true);
+        acc_hist(acc, hist_col(d * n + static_cast<int>((word >> (8 * (d & 3))) & 0xffu)), nslot, g);
       }
-      if constexpr (OBS) acc_obs(acc, ncol_h + kObsW * static_cast<int>(b.rec_obs[i]), g, true);
+      if constexpr (OBS) acc_obs(acc, ncol_h + kObsW * static_cast<int>(b.rec_obs[i]), g);
     }
     acc_sums_to_lds(ls, acc);
     __syncthreads();
