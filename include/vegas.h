@@ -322,9 +322,10 @@ int vegas_stage_times(vegas_handle h, double *ms, int64_t *launches, int32_t res
  * dsigma_b/dtheta (device outputs sigma[B], dsigma[B][5]) over events
  * i < n_events of iteration index `iteration` at the handle's current grid:
  * common random numbers for all points, the proposal (grid, Breit-Wigner and
- * tau mappings) held at the handle's nominal parameters, a hand-written reverse
- * sweep through |M|^2 and the PDFs per (event, point).  Results do not depend
- * on the launch configuration.  Asynchronous on the stream; scratch of
+ * tau mappings) held at the handle's nominal parameters, the derivatives of
+ * |M|^2 and the PDFs in closed form per (event, point).  Results do not depend
+ * on the launch configuration; a point's last bits do on B, which sets the order
+ * of its sums.  Asynchronous on the stream; scratch of
  * 8 * 6 * B * (ceil(n/64) + ceil(n/16384)) bytes is allocated by the library on
  * first use and kept until vegas_destroy.  (Paper Sec. 2.1 fixes the estimator;
  * the derivative is this library's extension.)

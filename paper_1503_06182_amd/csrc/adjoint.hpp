@@ -1,4 +1,4 @@
-// adjoint.hpp -- hand-written reverse sweep of the Drell-Yan VEGAS estimator with
+// adjoint.hpp -- hand-written adjoint of the Drell-Yan VEGAS estimator with
 // respect to theta = (M_Z, Gamma_Z, sin^2 theta_W, PDF exponent a, PDF exponent b).
 //
 // sigma(theta) = (1/N) sum_i w_i(theta) at a fixed grid and a fixed random stream

@@ -442,7 +442,12 @@ __device__ __forceinline__ int64_t batch_at(const BatchIdx& x, int64_t i) {
 // ---------------------------------------------------------------------------
 constexpr int kEvTile = 16;
 constexpr int kWgSplit = 256;  // events per split of the weight gradients (more above kFusedBatch)
-constexpr int64_t kFusedBatch = 16384;  // above: one layer's operands at a time (17 KB per event for all six)
+// batches of up to this many events keep the weight gradients' operands of all six layers (18 KB
+// per event) and run in one launch; larger ones keep one layer's.  The one launch is the faster
+// at every size measured (loss and gradient of 4096 events 94 us against 254 layer by layer,
+// 16384 278 and 409, 65536 1023 and 1273), so the line is drawn by the memory: 240 MB more up
+// to here, 970 MB up to 65536 for the last fifth
+constexpr int64_t kFusedBatch = 16384;
 
 template <int KS>
 struct WFrags {  // two 16-column blocks of a wave, KS steps of 32
@@ -1036,7 +1041,7 @@ int flow_prep(vegas_flow_state* f) {
 // less for each CU, take 40.4 to 41.0 throughout (and the six launches of before took 50)
 constexpr int64_t kFusedDensity = 2 * 256 * kEvTile;
 
-// forward-kernel blocks: three resident per CU (LDS 44 KB, at most 168 VGPRs); more tiles
+// forward-kernel blocks: three resident per CU (LDS 52 KB, at most 168 VGPRs); more tiles
 // per block amortise the per-launch load of the weights into registers
 constexpr int kFwdBlocks = 3 * 256;
 
