@@ -326,8 +326,8 @@ int vegas_stage_times(vegas_handle h, double *ms, int64_t *launches, int32_t res
  * |M|^2 and the PDFs in closed form per (event, point).  Results do not depend
  * on the launch configuration; a point's last bits do on B, which sets the order
  * of its sums.  Asynchronous on the stream; scratch of
- * 8 * 6 * B * (ceil(n/64) + ceil(n/16384)) bytes is allocated by the library on
- * first use and kept until vegas_destroy.  (Paper Sec. 2.1 fixes the estimator;
+ * 8 * 6 * B * (R + ceil(R/256)) bytes, R = min(ceil(n/64), 4096), is allocated by the
+ * library on first use and kept until vegas_destroy.  (Paper Sec. 2.1 fixes the estimator;
  * the derivative is this library's extension.)
  * Errors: VEGAS_EINVAL (other process, B or n out of range, NULL), VEGAS_ENOMEM. */
 int vegas_grad(vegas_handle h, const double *params_dev, int32_t B, int64_t n_events, uint32_t iteration,
@@ -336,9 +336,9 @@ int vegas_grad(vegas_handle h, const double *params_dev, int32_t B, int64_t n_ev
 /* vegas_grad without any device allocation, for callers that cannot allocate:
  * code under HIP graph capture, tight serving loops, harnesses that forbid it.
  * Same arguments, kernels, results (bit for bit) and errors as vegas_grad, but
- * the per-tile partials and the tree's first level live in a static device
+ * the partials and the tree's first level live in a static device
  * array of VEGAS_SCRATCH_DOUBLES binary64 values (16 MiB) that the library
- * holds on each GPU it runs on until the process ends; a call needs
+ * holds on each GPU it runs on until the process ends; a call is taken to need
  * (T + ceil(T / 256)) * 6 * B of them, T = ceil(n_events / 64) (at B = 64 up
  * to about 3.4e5 events, at B = 8 about 2.7e6).  Every call on one GPU shares
  * that GPU's array: calls that overlap on one GPU (other streams, other

@@ -3129,14 +3129,19 @@ int vegas_get_weights(vegas_handle h, int64_t first, int64_t n, double* w, uint8
 }
 
 namespace {
-// doubles of adjoint scratch a call may ask for: a row of partials per 64-event tile
-// ([ceil(n/64)][6][B]) and the first level of the fixed tree over them -- the documented
-// size; rows of several tiles need less of it
-size_t grad_scratch_doubles(int32_t B, int64_t n_events) {
-  const int64_t ntiles = (n_events + 63) / 64;
-  const int64_t lvl1 = (ntiles + kTreeRows - 1) / kTreeRows;
-  return static_cast<size_t>((ntiles + lvl1) * kGradVals * B);
+// doubles of adjoint scratch for `rows` rows of partials ([rows][6][B]) and the first level of
+// the fixed tree over them
+size_t grad_doubles(int32_t B, int64_t rows) {
+  return static_cast<size_t>((rows + (rows + kTreeRows - 1) / kTreeRows) * kGradVals * B);
 }
+// what a call uses at most: rows of several tiles once there are more than kGradRows tiles
+// (not the row count itself, which falls where rows take another tile: a smaller call never
+// needs more)
+size_t grad_scratch_doubles(int32_t B, int64_t n_events) {
+  return grad_doubles(B, std::min<int64_t>((n_events + 63) / 64, kGradRows));
+}
+// the size that the allocation-free call is documented to ask for, a row per 64-event tile
+size_t grad_noalloc_doubles(int32_t B, int64_t n_events) { return grad_doubles(B, (n_events + 63) / 64); }
 
 int grad_check(vegas_handle h, const double* params_dev, int32_t B, int64_t n_events, double* sigma_dev,
                double* dsigma_dev) {
@@ -3146,7 +3151,7 @@ int grad_check(vegas_handle h, const double* params_dev, int32_t B, int64_t n_ev
   return VEGAS_OK;
 }
 
-// the adjoint's launches with the scratch at buf (>= grad_scratch_doubles(B, n) doubles)
+// the adjoint's launches with the scratch at buf (at least grad_scratch_doubles(B, n) doubles)
 int grad_launch(vegas_handle h, const double* params_dev, int32_t B, int64_t n_events, uint32_t iteration,
                 double* sigma_dev, double* dsigma_dev, double* buf) {
   const int64_t ntiles = (n_events + 63) / 64;
@@ -3225,7 +3230,7 @@ int vegas_grad_noalloc(vegas_handle h, const double* params_dev, int32_t B, int6
                        double* sigma_dev, double* dsigma_dev) {
   const int v = grad_check(h, params_dev, B, n_events, sigma_dev, dsigma_dev);
   if (v != VEGAS_OK) return v;
-  if (grad_scratch_doubles(B, n_events) > VEGAS_SCRATCH_DOUBLES) return VEGAS_ETOOBIG;
+  if (grad_noalloc_doubles(B, n_events) > VEGAS_SCRATCH_DOUBLES) return VEGAS_ETOOBIG;
   if (!h->scratch) {
     g_last_hip_error = h->scratch_error;
     return VEGAS_EHIP;
